@@ -1,4 +1,5 @@
-// Tiled MFMA GEMM for the fully connected layers of the path:
+// Tiled MFMA GEMM for the fully connected layers of the path, staged through
+// registers: fp32, and bf16 with a GELU on A (other bf16 layers: gemm_dma.hip)
 //   out[R, Cout] = act_out(act_in(A)[R, K] W[Cout, K]^T + b) + residual
 //   * the MRConv update over materialised [x | m] rows for wide channels
 //     (Sec. II-A Eq. 3; the W_x / W_m split of Sec. IV-C2 is the two halves of
@@ -51,8 +52,6 @@ struct GemmCfg {
   // stage, so their tiles are not double-buffered
   static constexpr size_t kSmem = (size_t)(STEP == 384 || STEP == 192 ? 2 : 4) * kTile;
 };
-
-size_t gemm_smem_bytes() { return GemmCfg<128, 128>::kSmem; }
 
 // GELU of the 16-byte vector's elements, rounded back to the storage type.
 template <int DT>
@@ -264,19 +263,20 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(BM == 1
   }
 }
 
+// v: act_out + 2 act_in (fp32), or act_out + 4 (bf16 with a GELU on A).
 template <int BM, int STEP, int NW = 4>
 const void* gemm_fn(int v) {
-  static const void* const fns[8] = {
+  static const void* const fns[6] = {
       (const void*)&gemm_nt_kernel<0, 0, 0, BM, STEP, NW>, (const void*)&gemm_nt_kernel<0, 0, 1, BM, STEP, NW>,
       (const void*)&gemm_nt_kernel<0, 1, 0, BM, STEP, NW>, (const void*)&gemm_nt_kernel<0, 1, 1, BM, STEP, NW>,
-      (const void*)&gemm_nt_kernel<1, 0, 0, BM, STEP, NW>, (const void*)&gemm_nt_kernel<1, 0, 1, BM, STEP, NW>,
       (const void*)&gemm_nt_kernel<1, 1, 0, BM, STEP, NW>, (const void*)&gemm_nt_kernel<1, 1, 1, BM, STEP, NW>};
   return fns[v];
 }
 
 hipError_t launch_gemm_nt(const GemmArgs& a, int dt_bf16, hipStream_t stream, hipEvent_t ev0,
                           hipEvent_t ev1) {
-  const int v = (dt_bf16 ? 4 : 0) + (a.act_in ? 2 : 0) + (a.act_out ? 1 : 0);
+  if (dt_bf16 && !a.act_in) return launch_gemm_dma(a, stream, ev0, ev1);
+  const int v = (dt_bf16 ? 4 : a.act_in ? 2 : 0) + (a.act_out ? 1 : 0);
   const size_t rowb = (size_t)a.K * (dt_bf16 ? 2 : 4);
   // large tiles once they alone give every CU a tile and K is long
   const long tiles128 = (long)((a.R + 127) / 128) * ((a.Cout + 127) / 128);

@@ -65,6 +65,30 @@ __device__ __forceinline__ f32x4 mfma_f32(float a, float b, f32x4 acc) {
 }
 
 // ---------------------------------------------------------------------------
+// direct loads from global memory into LDS (gfx950: 16 bytes per lane).  Lane l's
+// bytes land at lds + 16 l.  Written as asm because the compiler, which cannot
+// tell a load's LDS place from the reads of another buffer, would wait for all
+// of them before every LDS read; dma_wait_barrier() is the one wait that counts.
+// No register is written, so nothing the compiler allocates is in flight.
+// ---------------------------------------------------------------------------
+static __device__ __align__(16) const uint32_t kZero16[4] = {0, 0, 0, 0};  // source of zeros
+
+__device__ __forceinline__ uint32_t lds_offset(const void* p) {
+  return (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) char*)p;
+}
+
+// `lds` is wave-uniform (it goes to M0); lanes that are off write nothing.
+__device__ __forceinline__ void lds_dma16(const void* g, uint32_t lds) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(lds), "v"(g) : "memory");
+}
+
+// This wave's direct loads have landed and its LDS reads are done; then the
+// workgroup's barrier.
+__device__ __forceinline__ void dma_wait_barrier() {
+  asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+}
+
+// ---------------------------------------------------------------------------
 // cross-lane moves inside each row of 16 lanes, as DPP modifiers (no LDS trip)
 // ---------------------------------------------------------------------------
 template <int CTRL>

@@ -125,9 +125,10 @@ int mrconv_headw_steps(int hd, int dt_bf16);
 hipError_t launch_mrconv_headw(const MrArgs& a, int dt_bf16, int rt, hipStream_t stream);
 hipError_t launch_expand_heads(const void* Wh, void* Wd, int C, int heads, int dt_bf16,
                                hipStream_t stream);
-size_t gemm_smem_bytes();
 hipError_t launch_gemm_nt(const GemmArgs& a, int dt_bf16, hipStream_t stream, hipEvent_t ev0,
                           hipEvent_t ev1);
+// Its bf16 layers without a GELU on A (gemm_dma.hip); launch_gemm_nt calls it.
+hipError_t launch_gemm_dma(const GemmArgs& a, hipStream_t stream, hipEvent_t ev0, hipEvent_t ev1);
 
 MrArgs make_mr_args(const void* x, const void* keys, const int32_t* idx, const void* W,
                     const void* bias, void* out, int B, int N, int M, int C, int Cout, int k);

@@ -1,0 +1,58 @@
+"""GPU parity of the bf16 GEMM's tiles (gl_linear) against the CPU oracle, at
+the sizes where each can go wrong: one row or column past a tile, a partial or
+a single K stage, rows of the output or residual that are not 16-byte aligned,
+the residual updated in place."""
+import numpy as np
+import pytest
+import torch
+
+import oracle as O
+from gpu_helpers import check_close, from_dev, require_gpu, to_dev
+from paper_2604_21290_amd import inputs as I
+
+pytestmark = pytest.mark.gpu
+
+CASES = [
+    # label, R, K, Cout, act_out, residual, bias, offset of out and residual in elements
+    ("128x128_one_row_past", 128 * 191 + 1, 72, 250, 1, True, True, 0),
+    ("128x128_whole_stage", 128 * 192, 64, 256, 0, True, False, 0),
+    ("128x128_short_last_tile", 128 * 400 - 3, 136, 80, 0, True, True, 0),
+    ("128x64_padding_rule", 128 * 200 + 5, 80, 160, 0, True, True, 0),
+    ("128x64_three_column_tiles", 128 * 127 + 65, 200, 136, 1, False, True, 0),
+    ("128x64_residual", 128 * 383 + 1, 8, 64, 0, True, True, 0),
+    ("64x64_ragged", 641, 136, 776, 1, True, True, 0),
+    ("64x64_unaligned_out", 1300, 192, 448, 0, True, True, 1),
+    ("64x64_aligned_8_bytes", 1300, 64, 456, 0, True, False, 4),
+    ("32x64_ragged", 33, 264, 65, 0, True, True, 0),
+    ("32x64_two_k_stages", 65, 128 + 8, 72, 1, False, True, 0),
+    ("32x64_one_element", 1, 8, 1, 0, True, True, 0),
+]
+
+
+@pytest.mark.parametrize("case", CASES, ids=[c[0] for c in CASES])
+def test_bf16_tiles(case):
+    require_gpu()
+    from paper_2604_21290_amd import api
+    label, R, K, Co, act, with_res, with_bias, off = case
+    g = np.random.default_rng(R + 3 * K + Co)
+    x = I.store(g.standard_normal((R, K)), I.BF16)
+    W = I.store(g.uniform(-1, 1, (Co, K)) / np.sqrt(K), I.BF16)
+    b = I.store(g.uniform(-0.5, 0.5, Co), I.BF16) if with_bias else None
+    r = I.store(g.standard_normal((R, Co)), I.BF16) if with_res else None
+    print("[gpu-test] gemm", label, flush=True)
+    guard = torch.full((R * Co + 64,), 7.0, dtype=torch.bfloat16, device="cuda")
+    out = guard[off:off + R * Co].view(R, Co)
+    if with_res:
+        out.copy_(to_dev(r))  # the residual, updated in place
+    api.linear(to_dev(x), to_dev(W), None if b is None else to_dev(b), 0, act,
+               out if with_res else None, out=out)
+    torch.cuda.synchronize()
+    lin = O.linear_ref(x.value, W.value, None if b is None else b.value)
+    ref = O.gelu_ref(lin) if act else lin
+    mag = np.abs(x.value) @ np.abs(W.value).T + (np.abs(b.value) if b is not None else 0.0)
+    if r is not None:
+        ref, mag = ref + r.value, mag + np.abs(r.value)
+    # one rounding of the output and a K-term fp32 sum (GELU's slope is below 1.13)
+    check_close(from_dev(out).value, ref, I.BF16, label, mag=1.13 * mag, n_terms=K)
+    rest = torch.cat([guard[:off], guard[off + R * Co:]])
+    assert bool((rest == 7.0).all()), (label, "wrote past the output")
