@@ -96,48 +96,44 @@ __device__ __forceinline__ uint32_t dpp_mov(uint32_t v) {
   return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, CTRL, 0xF, 0xF, false);
 }
 
-// value of lane t ^ j (j = 1, 2, 4 or 8) within the lane's row of 16
-__device__ __forceinline__ uint32_t lane_xor16(uint32_t v, int j) {
-  switch (j) {
-    case 1: return dpp_mov<0xB1>(v);                     // quad_perm [1,0,3,2]
-    case 2: return dpp_mov<0x4E>(v);                     // quad_perm [2,3,0,1]
-    case 4: return dpp_mov<0x1B>(dpp_mov<0x141>(v));     // half-row mirror, then quad reverse
-    default: return dpp_mov<0x128>(v);                   // row rotate by 8
-  }
-}
-
 // value of lane 15 - t within the lane's row of 16
 __device__ __forceinline__ uint32_t lane_reverse16(uint32_t v) { return dpp_mov<0x140>(v); }
 
-// min (low) or max (!low) of v and the value of lane t ^ (1 << j) in the
-// lane's row of 16.  The minimum and the maximum each read the partner through
-// a DPP move of their own whose unused `old` operand is the operation's
-// identity, so the compiler folds each move into its v_min_u32 / v_max_u32
-// (every lane's source is inside its row, so `old` never reaches a result).
-template <int CTRL>
-__device__ __forceinline__ uint32_t dpp_min(uint32_t v, uint32_t src) {
-  return min(v, (uint32_t)__builtin_amdgcn_update_dpp((int)0xffffffffu, (int)src, CTRL, 0xF, 0xF, false));
+// median of three (one v_med3_u32): the minimum of a and b with c = 0, their
+// maximum with c = ~0
+__device__ __forceinline__ uint32_t med3_u32(uint32_t a, uint32_t b, uint32_t c) {
+  return max(min(a, b), min(max(a, b), c));
 }
-template <int CTRL>
-__device__ __forceinline__ uint32_t dpp_max(uint32_t v, uint32_t src) {
-  return max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)src, CTRL, 0xF, 0xF, false));
-}
-// Both results are computed by every lane (a DPP read in lane-divergent
-// control flow would see inactive partners) and the wanted one selected.
-__device__ __forceinline__ uint32_t lane_cas16(uint32_t v, int j, bool low) {
-  uint32_t mn, mx;
+
+// Compare-exchange of a lane with its partner in its row of 16: the lower lane
+// of the pair keeps the minimum, the upper one the maximum.  One DPP move of the
+// partner's value and one median, whose third operand is 0 in lower lanes and
+// all ones in upper ones (bit `b` of t tells which: the highest bit in which the
+// partners differ).  A minimum, a maximum and a select took three instructions.
+__device__ __forceinline__ uint32_t upper_mask(int t, int b) { return 0u - ((uint32_t)(t >> b) & 1u); }
+
+// partner t ^ (1 << j)
+__device__ __forceinline__ uint32_t lane_cas16(uint32_t v, int j, int t) {
+  uint32_t p;
   switch (j) {
-    case 0: mn = dpp_min<0xB1>(v, v); mx = dpp_max<0xB1>(v, v); break;    // quad_perm [1,0,3,2]
-    case 1: mn = dpp_min<0x4E>(v, v); mx = dpp_max<0x4E>(v, v); break;    // quad_perm [2,3,0,1]
-    case 2: {                                                              // half-row mirror,
-      const uint32_t m = dpp_mov<0x141>(v);                                // then quad reverse
-      mn = dpp_min<0x1B>(v, m);
-      mx = dpp_max<0x1B>(v, m);
-      break;
-    }
-    default: mn = dpp_min<0x128>(v, v); mx = dpp_max<0x128>(v, v); break;  // row rotate by 8
+    case 0: p = dpp_mov<0xB1>(v); break;                  // quad_perm [1,0,3,2]
+    case 1: p = dpp_mov<0x4E>(v); break;                  // quad_perm [2,3,0,1]
+    case 2: p = dpp_mov<0x1B>(dpp_mov<0x141>(v)); break;  // half-row mirror, then quad reverse
+    default: p = dpp_mov<0x128>(v); break;                // row rotate by 8
   }
-  return low ? mn : mx;
+  return med3_u32(v, p, upper_mask(t, j));
+}
+
+// partner t ^ (2^s - 1), s = 1..4: the pairs that fold a run of 2^s onto itself
+__device__ __forceinline__ uint32_t lane_fold16(uint32_t v, int s, int t) {
+  uint32_t p;
+  switch (s) {
+    case 1: p = dpp_mov<0xB1>(v); break;    // quad_perm [1,0,3,2]
+    case 2: p = dpp_mov<0x1B>(v); break;    // quad reverse
+    case 3: p = dpp_mov<0x141>(v); break;   // half-row mirror
+    default: p = dpp_mov<0x140>(v); break;  // row mirror
+  }
+  return med3_u32(v, p, upper_mask(t, s - 1));
 }
 
 // value of lane (16*(lane/16) + src) for a wave-uniform src in [0, 16)

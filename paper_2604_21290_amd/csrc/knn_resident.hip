@@ -99,9 +99,9 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(KS > 4 
 #pragma unroll
   for (int u = 0; u < NV; ++u) {
     const int i = min(tid + NT * u, total - 1);
-    const int r = (int)(((uint32_t)i * magic) >> 16), v = i - r * nvec;
-    dst[u] = r * stride + v * 16;
-    st[u] = *reinterpret_cast<const uint4*>(kb + ((size_t)min(r, M - 1) * nvec + v) * 16);
+    const int r = (int)(__umul24(i, magic) >> 16), v = i - __umul24(r, nvec);
+    dst[u] = __umul24(r, stride) + v * 16;
+    st[u] = *reinterpret_cast<const uint4*>(kb + (size_t)((__umul24(min(r, M - 1), nvec) + v) * 16));
   }
 #pragma unroll
   for (int u = 0; u < NV; ++u) *reinterpret_cast<uint4*>(smem + dst[u]) = st[u];
@@ -224,7 +224,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(KS > 4 
 #pragma unroll
     for (int e = 0; e < R; ++e) L[e] = 0xffffffffu;
     uint32_t tau = 0xffffffffu;
-    select_chunk<R>(L, tau, c16, KK, t, lane);
+    select_chunk<R, KT, true>(L, tau, c16, KK, t, lane);
     const int row = q0 + 16 * w + 4 * g + v;
     if (row < N) {
       int32_t* o = a.idx + ((size_t)b * N + row) * k;

@@ -35,17 +35,17 @@ constexpr int kKnnThreads = 256;
 constexpr int kKnnKU = 3;        // k-steps whose operands are loaded as one batch
 constexpr int kKnnTPP = 4;       // key tiles of a chunk per wave, computed in one pass
 
-// Sort one value per lane across each aligned row of 16 lanes (ascending).
-// All cross-lane moves are DPP modifiers within the row.
+// Sort one value per lane across each aligned row of 16 lanes (ascending): a
+// bitonic sort whose merges start by folding two ascending runs onto each other
+// (partner t ^ (2^s - 1)), so every compare-exchange keeps the minimum in the
+// lower lane.  All cross-lane moves are DPP moves within the row: 21
+// instructions, 33 as minimum, maximum and select.
 __device__ __forceinline__ uint32_t sort16_lanes(uint32_t c, int t) {
 #pragma unroll
   for (int s = 1; s <= 4; ++s) {
+    c = lane_fold16(c, s, t);
 #pragma unroll
-    for (int j = s - 1; j >= 0; --j) {
-      const bool up = ((t >> s) & 1) == 0;
-      const bool lower = ((t >> j) & 1) == 0;
-      c = lane_cas16(c, j, lower == up);
-    }
+    for (int j = s - 2; j >= 0; --j) c = lane_cas16(c, j, t);
   }
   return c;
 }
@@ -67,7 +67,7 @@ __device__ __forceinline__ void merge16_into_list(uint32_t* L, uint32_t c, int t
   for (int j = 3; j >= 0; --j) {
 #pragma unroll
     for (int a = 0; a < R; ++a) {
-      L[a] = lane_cas16(L[a], j, ((t >> j) & 1) == 0);
+      L[a] = lane_cas16(L[a], j, t);
     }
   }
 }
@@ -83,90 +83,90 @@ __device__ __forceinline__ uint32_t list_element(const uint32_t* L, int e, int l
   return row_broadcast16(v, e & 15, lane);
 }
 
-// The 4 smallest of a lane's 16 values, ascending, in v[0..3]; v[4..15] hold
-// the other 12 in no order.  Four sorted groups of 4 (five comparators each),
-// then three merges that keep the 4 smallest of two sorted groups sorted
-// (a half-cleaner against the reversed second group, then a 4-element
-// bitonic sort): 44 compare-exchanges against the full bitonic sort's 80.
-__device__ __forceinline__ void top4_regs_asc(uint32_t (&v)[16]) {
+// The NT smallest of a lane's first NV values, ascending, in m: each value is
+// inserted by NT medians (m[q] = median of m[q-1], m[q] and the value).
+template <int NT, int NV>
+__device__ __forceinline__ void top_regs_asc(uint32_t (&m)[NT], const uint32_t (&v)[16]) {
 #pragma unroll
-  for (int q = 0; q < 16; q += 4) {
-    cas_asc(v[q], v[q + 1]);
-    cas_asc(v[q + 2], v[q + 3]);
-    cas_asc(v[q], v[q + 2]);
-    cas_asc(v[q + 1], v[q + 3]);
-    cas_asc(v[q + 1], v[q + 2]);
+  for (int q = 0; q < NT; ++q) m[q] = 0xffffffffu;
+#pragma unroll
+  for (int e = 0; e < NV; ++e) {
+#pragma unroll
+    for (int q = NT - 1; q > 0; --q) m[q] = med3_u32(m[q - 1], m[q], v[e]);
+    m[0] = min(m[0], v[e]);
   }
-  auto merge4 = [&](int a, int b) {
-#pragma unroll
-    for (int i = 0; i < 4; ++i) cas_asc(v[a + i], v[b + 3 - i]);
-    cas_asc(v[a], v[a + 2]);
-    cas_asc(v[a + 1], v[a + 3]);
-    cas_asc(v[a], v[a + 1]);
-    cas_asc(v[a + 2], v[a + 3]);
-  };
-  merge4(0, 4);
-  merge4(8, 12);
-  merge4(0, 8);
 }
 
-// Merge this lane's 16 candidates v (one row per 16 lanes) into the row's
-// sorted list L of the KK smallest keys; tau is the list's KK-th key (all ones
-// while the list is not full).  Candidates not below tau are dropped first; the
-// rest are sorted per lane and merged 16 at a time, smallest first.
+// Sort and merge the runs a and b (one value per lane each); the two sorts are
+// independent chains that the scheduler interleaves.
 template <int R>
+__device__ __forceinline__ void merge_two(uint32_t* L, uint32_t a, uint32_t b, int t) {
+  const uint32_t c0 = sort16_lanes(a, t);
+  const uint32_t c1 = sort16_lanes(b, t);
+  merge16_into_list<R>(L, c0, t);
+  merge16_into_list<R>(L, c1, t);
+}
+
+// Merge this lane's candidates v[0 .. NV-1] (one row per 16 lanes) into the row's
+// sorted list L of the KK smallest keys; tau is the list's KK-th key (all ones
+// while the list is not full).  FIRST: the list is empty.
+//   A lane's few smallest candidates are ordered first (4, 6 or 8 by the length
+//   of the list: of 16 lanes' candidates the KK smallest rarely include more of
+//   one lane), then merged a layer of 16 at a time, one per lane, smallest
+//   first, until no lane's next one is below the list's KK-th key.  Merging a
+//   key that is not below it changes nothing among the first KK elements
+//   (keys are unique).  Only when a lane's last ordered candidate is below it
+//   are the lane's others looked at.  In the 196-key builds of k = 9 this takes
+//   about 170 instructions a row of 16 lanes, against 305 with the four smallest
+//   from a network of 44 comparators and four layers merged.
+template <int R, int NV, bool FIRST>
 __device__ __forceinline__ void select_chunk(uint32_t* L, uint32_t& tau, uint32_t (&v)[16], int KK,
                                              int t, int lane) {
-  bool pass = false;
+  constexpr int NT = R == 1 ? 4 : R == 2 ? 6 : 8;
+  uint32_t m[NT];
+  top_regs_asc<NT, NV>(m, v);
+  if constexpr (FIRST) {
+    // KK <= 16 R keys below the threshold need not exist before R layers are in
+    L[0] = sort16_lanes(m[0], t);
+    merge16_into_list<R>(L, sort16_lanes(m[1], t), t);
+    if constexpr (R >= 2) merge_two<R>(L, m[2], m[3], t);
+    tau = list_element<R>(L, KK - 1, lane);
+  }
+  // One layer at a time where the list is short and its second layer is rarely
+  // the last but one needed, two where most are
+  constexpr int Q0 = !FIRST ? 0 : R == 1 ? 2 : 4;
+  if constexpr (R == 1) {
 #pragma unroll
-  for (int m = 0; m < 16; ++m) pass |= v[m] < tau;
-  if (__any(pass)) {
-#pragma unroll
-    for (int m = 0; m < 16; ++m) v[m] = v[m] < tau ? v[m] : 0xffffffffu;
-    if constexpr (R == 1) {
-      // A list of at most 16 rarely takes more than each lane's 4 smallest:
-      // those are ordered first, and the rest only when some lane's fifth
-      // smallest is still below the threshold after them.
-      top4_regs_asc(v);
-#pragma unroll
-      for (int m = 0; m < 4; m += 2) {
-        if (!__any(v[m] < tau)) return;
-        const uint32_t c0 = sort16_lanes(v[m], t);
-        const uint32_t c1 = sort16_lanes(v[m + 1], t);
-        merge16_into_list<R>(L, c0, t);
-        merge16_into_list<R>(L, c1, t);
-        tau = list_element<R>(L, KK - 1, lane);
-      }
-      uint32_t fifth = v[4];
-#pragma unroll
-      for (int m = 5; m < 16; ++m) fifth = min(fifth, v[m]);
-      if (!__any(fifth < tau)) return;
-      sort_regs_asc<16>(v);  // v[0..3] are already the smallest four, in order
-#pragma unroll
-      for (int m = 4; m < 16; m += 2) {
-        if (!__any(v[m] < tau)) break;
-        const uint32_t c0 = sort16_lanes(v[m], t);
-        const uint32_t c1 = sort16_lanes(v[m + 1], t);
-        merge16_into_list<R>(L, c0, t);
-        merge16_into_list<R>(L, c1, t);
-        tau = list_element<R>(L, KK - 1, lane);
-      }
-      return;
-    }
-    sort_regs_asc<16>(v);
-    // Two layers per pass: their 16-lane sorts are independent chains that
-    // the scheduler interleaves.  The second layer may hold no key below the
-    // updated tau; merging it then changes nothing among the first KK list
-    // elements (keys are unique, so none of them can be displaced).
-#pragma unroll
-    for (int m = 0; m < 16; m += 2) {
-      if (!__any(v[m] < tau)) break;
-      const uint32_t c0 = sort16_lanes(v[m], t);
-      const uint32_t c1 = sort16_lanes(v[m + 1], t);
-      merge16_into_list<R>(L, c0, t);
-      merge16_into_list<R>(L, c1, t);
+    for (int q = Q0; q < NT; ++q) {
+      if (!__any(m[q] < tau)) return;
+      merge16_into_list<R>(L, sort16_lanes(m[q], t), t);
       tau = list_element<R>(L, KK - 1, lane);
     }
+  } else {
+#pragma unroll
+    for (int q = Q0; q < NT; q += 2) {
+      if (!__any(m[q] < tau)) return;
+      merge_two<R>(L, m[q], m[q + 1], t);
+      tau = list_element<R>(L, KK - 1, lane);
+    }
+  }
+  // a lane whose last ordered candidate is not below tau has no other that is
+  if (NV <= NT || !__any(m[NT - 1] < tau)) return;
+  bool pass = false;
+#pragma unroll
+  for (int e = 0; e < NV; ++e) {
+    v[e] = v[e] > m[NT - 1] ? v[e] : 0xffffffffu;
+    pass |= v[e] < tau;
+  }
+#pragma unroll
+  for (int e = NV; e < 16; ++e) v[e] = 0xffffffffu;
+  if (!__any(pass)) return;
+  sort_regs_asc<16>(v);
+#pragma unroll
+  for (int e = 0; e < 16 - NT; e += 2) {
+    if (!__any(v[e] < tau)) return;
+    merge_two<R>(L, v[e], v[e + 1], t);
+    tau = list_element<R>(L, KK - 1, lane);
   }
 }
 
@@ -304,7 +304,8 @@ __device__ __forceinline__ void knn_tile(char* smem, const char* __restrict__ xb
     }
     __syncthreads();  // the strip is free for the next chunk
 
-    select_chunk<R>(L, tau, v, KK, t, lane);
+    if (chunk0 == 0) select_chunk<R, 16, true>(L, tau, v, KK, t, lane);
+    else select_chunk<R, 16, false>(L, tau, v, KK, t, lane);
   }
 
   // -- dilation and output: idx[row, e/dil] = index of list element e ---------

@@ -250,7 +250,7 @@ __device__ __forceinline__ void knn_wide_tile(char* smem, const KnnArgs& a, int 
 #pragma unroll
     for (int q = 0; q < R; ++q) L[q] = 0xffffffffu;
     uint32_t tau = 0xffffffffu;
-    select_chunk<R>(L, tau, v, KK, t, lane);
+    select_chunk<R, KROWS / 16, true>(L, tau, v, KK, t, lane);
     const int row = q0 + rl;
     if (row < N) {
       int32_t* o = a.idx + ((size_t)b * N + row) * k;

@@ -218,3 +218,52 @@ def test_pool_edges():
         check_close(got, O.pool_keys_ref(x.value, H, W, r), dt, "pool edge")
         if r == 1:
             assert np.array_equal(got, x.value)
+
+
+# -- one lane's keys nearest ---------------------------------------------------------
+ONE_LANE = [
+    # label, B, N, M, C, k, d, dtype: the kernel that builds the graph
+    ("tile_r1_fp32", 1, 40, 196, 36, 9, 1, I.F32),
+    ("tile_r2", 1, 40, 256, 80, 9, 2, I.BF16),
+    ("tile_r4_fp32", 2, 17, 196, 64, 12, 3, I.F32),
+    ("wide_r1", 2, 50, 196, 192, 9, 1, I.BF16),
+    ("wide_r1_k16", 1, 33, 250, 136, 16, 1, I.BF16),
+    ("wide_r2", 2, 50, 196, 192, 9, 3, I.BF16),
+    ("wide_r4", 1, 50, 224, 320, 16, 4, I.BF16),
+    ("wide_few_keys", 2, 50, 49, 192, 9, 1, I.BF16),
+    ("resident_r1", 8, 3136, 196, 80, 9, 1, I.BF16),
+    ("resident_r2", 8, 3136, 208, 64, 9, 2, I.BF16),
+    ("resident_r4_16_tiles", 8, 3136, 256, 40, 16, 4, I.BF16),
+    ("stream_r1", 1, 130, 700, 96, 9, 1, I.BF16),
+    ("stream_r4_fp32", 1, 65, 520, 52, 12, 4, I.F32),
+]
+
+
+@pytest.mark.parametrize("case", ONE_LANE, ids=[c[0] for c in ONE_LANE])
+def test_nearest_keys_in_one_lane(case):
+    """The selection keeps a lane's few smallest candidates in order and looks at
+    its others only when those may not do.  Here the nearest keys of every row
+    are those of one lane (indices 5, 21, 37, ...), at angles far enough apart
+    to rank the same in any precision."""
+    require_gpu()
+    from paper_2604_21290_amd import api
+    label, B, N, M, C, k, d, dt = case
+    g = np.random.default_rng(M + C)
+    u = g.standard_normal(C)
+    u /= np.linalg.norm(u)
+    keys = g.standard_normal((M, C))
+    keys -= (keys @ u)[:, None] * u          # everything else at right angles to u
+    keys /= np.linalg.norm(keys, axis=1, keepdims=True)
+    lane = np.arange(5, M, 16)
+    ang = g.permutation(0.1 + 1.2 * np.arange(len(lane)) / len(lane))
+    keys[lane] = np.cos(ang)[:, None] * u + np.sin(ang)[:, None] * keys[lane]
+    x = u + 0.02 * g.standard_normal((B, N, C)) / np.sqrt(C)
+    xs, ks = I.store(x, dt), I.store(np.broadcast_to(keys, (B, M, C)).copy(), dt)
+    print("[gpu-test] one lane", label, flush=True)
+    idx = api.knn_graph(to_dev(xs), k, d, keys=to_dev(ks))
+    torch.cuda.synchronize()
+    rows = np.unique(np.linspace(0, N - 1, 40).astype(int))
+    got = idx.cpu().numpy()
+    check_idx(got, O.knn_distances(xs.value, ks.value, rows=rows), k, d, rows=rows, label=label)
+    near = min(len(lane), k * d)
+    assert (got[:, :, :(near + d - 1) // d] % 16 == 5).all(), label
