@@ -882,11 +882,18 @@ gl_status check_vig_params(const gl_vig_params* p, int C, gl_dtype dt) {
 
 // One full block on the handle's streams.  u holds U^l (computed here, and
 // pooled into w.keys at pyramid stages, unless u_ready); idx_next (if any)
-// receives G(U^l, dil_next).
+// receives G(U^l, dil_next).  next (if any): the following block's weights, whose
+// FC1 (and key pooling) then overwrites u; every reader of U^l must be ahead on
+// the update stream, and the tail must run in one launch (vig_tail_fused).
+bool vig_tail_fused(const VigGrid& g, gl_dtype dt) {
+  return gl::mlp_use_fused(g.B * g.N(), g.C, dt == GL_BF16);
+}
+
 gl_status enqueue_vig_block(gl_lookahead_t h, const void* x_in, const VigGrid& g, int k,
                             const int32_t* idx_use, const gl_vig_params& p, gl_dtype dt,
                             const VigWs& w, void* u, bool u_ready, int32_t* idx_next,
-                            int dil_next, gl_schedule schedule, int rt, void* x_out) {
+                            int dil_next, gl_schedule schedule, int rt, void* x_out,
+                            const gl_vig_params* next = nullptr) {
   const int B = g.B, N = g.N(), M = g.M(), C = g.C, R = B * N, dtb = dt == GL_BF16;
   const void* keys = g.pooled() ? static_cast<const void*>(w.keys) : u;
   gl_status s;
@@ -950,6 +957,31 @@ gl_status enqueue_vig_block(gl_lookahead_t h, const void* x_in, const VigGrid& g
       return gl::launch_mrconv_args(ma, dtb, rt, mws, h->su, e0, e1);
     });
     if (s != GL_OK) return s;
+  }
+  if (vig_tail_fused(g, dt)) {
+    gl::MlpArgs ta{};
+    ta.s = w.ut;
+    ta.x = x_in;
+    ta.W_out = p.W_out;
+    ta.b_out = p.b_out;
+    ta.W_1 = p.W_1;
+    ta.b_1 = p.b_1;
+    ta.W_2 = p.W_2;
+    ta.b_2 = p.b_2;
+    ta.out = x_out;
+    if (next) {
+      ta.W_in = next->W_in;
+      ta.b_in = next->b_in;
+      ta.u_next = u;
+    }
+    ta.R = R;
+    ta.C = C;
+    s = timed_launch(h, GL_TIME_LINEAR, "block tail launch", [&](hipEvent_t e0, hipEvent_t e1) {
+      return gl::launch_mlp(ta, h->su, e0, e1);
+    });
+    if (s != GL_OK || !next || !g.pooled()) return s;
+    hipError_t e = gl::launch_pool(u, w.keys, B, g.H, g.W, C, g.r, dtb, h->su);
+    return e == hipSuccess ? GL_OK : hip_fail(e, "pool launch");
   }
   if ((s = lin("linear launch (FC2)", w.ut, C, p.W_out, p.b_out, C, 0, 0, x_in, w.y)) != GL_OK)
     return s;
@@ -1066,14 +1098,19 @@ gl_status gl_vig_stack(gl_lookahead_t h, const void* x0, int B, int H, int W, in
     });
   };
   if ((s = join_build(h)) != GL_OK) return s;
+  // The tail of block l also computes U^(l+1) in place of U^l where nothing off
+  // the update stream may still read U^l (the two-stream build does).
+  auto next_fc1 = [&](int l) -> const gl_vig_params* {
+    return l + 1 < L && schedule != GL_SCHED_LOOKAHEAD && vig_tail_fused(g, dt) ? &params[l + 1] : nullptr;
+  };
   if (schedule == GL_SCHED_STANDARD) {
     for (int l = 0; l < L; ++l) {
       const void* xi = l == 0 ? x0 : w.x[(l - 1) & 1];
       void* xo = l == L - 1 ? x_out : w.x[l & 1];
-      if ((s = project(xi, l)) != GL_OK) return s;
+      if ((l == 0 || !next_fc1(l - 1)) && (s = project(xi, l)) != GL_OK) return s;
       if ((s = build(dilations[l], w.idx[0])) != GL_OK) return s;
       if ((s = enqueue_vig_block(h, xi, g, k, w.idx[0], params[l], dt, w, w.u, true, nullptr, 0,
-                                 schedule, rt, xo)) != GL_OK)
+                                 schedule, rt, xo, next_fc1(l))) != GL_OK)
         return s;
     }
     return GL_OK;
@@ -1091,8 +1128,9 @@ gl_status gl_vig_stack(gl_lookahead_t h, const void* x0, int B, int H, int W, in
       next = 1 - cur;
       idx_next = w.idx[next];
     }
-    if ((s = enqueue_vig_block(h, xi, g, k, w.idx[cur], params[l], dt, w, w.u, l == 0, idx_next,
-                               idx_next ? dilations[l + 1] : 0, schedule, rt, xo)) != GL_OK)
+    if ((s = enqueue_vig_block(h, xi, g, k, w.idx[cur], params[l], dt, w, w.u,
+                               l == 0 || next_fc1(l - 1), idx_next, idx_next ? dilations[l + 1] : 0,
+                               schedule, rt, xo, next_fc1(l))) != GL_OK)
       return s;
     cur = next;
   }

@@ -45,6 +45,20 @@ struct GemmArgs {
   int act_in, act_out;   // 0 none, 1 GELU (on A's elements / on the pre-residual output)
 };
 
+// The row-local tail of a full ViG block (bf16): FC2 + residual, the FFN +
+// residual and, when u_next is given, FC1 of the next block.
+struct MlpArgs {
+  const void* s;        // [R, C] sigma(U~)
+  const void* x;        // [R, C] the block's input (FC2's residual)
+  const void *W_out, *b_out;   // [C, C]
+  const void *W_1, *b_1;       // [4C, C]
+  const void *W_2, *b_2;       // [C, 4C]
+  const void *W_in, *b_in;     // [C, C] FC1 of the next block
+  void* out;            // [R, C] the block's output
+  void* u_next;         // [R, C] FC1 of it, or null
+  int R, C;
+};
+
 // Workgroups are dispatched round-robin over the 8 XCDs (workgroup id mod 8).
 // Map dispatch ids so that consecutive logical ids (neighbouring tiles of the
 // same image, which share key rows) land on the same XCD and its L2.
@@ -129,6 +143,11 @@ hipError_t launch_gemm_nt(const GemmArgs& a, int dt_bf16, hipStream_t stream, hi
                           hipEvent_t ev1);
 // Its bf16 layers without a GELU on A (gemm_dma.hip); launch_gemm_nt calls it.
 hipError_t launch_gemm_dma(const GemmArgs& a, hipStream_t stream, hipEvent_t ev0, hipEvent_t ev1);
+
+// The tail of a full block in one launch (mlp.hip), for the shapes it is faster
+// at than its layers one by one; the same results.
+bool mlp_use_fused(int R, int C, int dt_bf16);
+hipError_t launch_mlp(const MlpArgs& a, hipStream_t stream, hipEvent_t ev0, hipEvent_t ev1);
 
 MrArgs make_mr_args(const void* x, const void* keys, const int32_t* idx, const void* W,
                     const void* bias, void* out, int B, int N, int M, int C, int Cout, int k);

@@ -396,3 +396,58 @@ def test_vig_stack_fused_equals_two_stream_full_size(name):
     la.close()
     assert torch.isfinite(fused.float()).all()
     assert torch.equal(fused, two), f"{name}: fused full-block stack differs from two-stream"
+
+
+# -- the one-launch tail of a block ---------------------------------------------------
+TAIL = [
+    # label, B, H, W, C, pool_r, bias: widths on both sides of a contraction step
+    # and of a column tile, rows past whole tiles of 16 and of 32 nodes
+    ("c8_one_wave_idle", 1, 3, 11, 8, 1, True),
+    ("c40_half_column_tile", 3, 7, 9, 40, 1, True),
+    ("c64", 2, 14, 14, 64, 1, False),
+    ("c96_two_rounds_of_32", 5, 29, 30, 96, 1, True),
+    ("c104_half_column_tile", 1, 10, 13, 104, 1, False),
+    ("c128_pooled", 2, 16, 16, 128, 2, True),
+    ("c136_padded_steps", 2, 9, 13, 136, 1, True),
+    ("c160_32_rows", 6, 28, 28, 160, 2, True),
+    ("c168_half_column_tile", 1, 12, 17, 168, 1, False),
+    ("c192_16_rows_last_tile_of_5", 21, 15, 13, 192, 1, False),
+    ("c200_layer_by_layer", 1, 12, 12, 200, 1, True),
+]
+
+
+@pytest.mark.parametrize("case", TAIL, ids=[c[0] for c in TAIL])
+def test_vig_tail(case):
+    """FC2, the FFN and the next block's FC1 in one launch: each block against the
+    oracle on the stored tensors, and every schedule's stack (whose fused form
+    also computes U of the next block there) bit for bit against the blocks,
+    whose FC1 is a launch of its own."""
+    require_gpu()
+    from paper_2604_21290_amd import api
+    label, B, H, W, C, r, bias = case
+    w = I.Workload(label, B, H, W, C, 4, (1, 2, 1), I.BF16, pool_r=r, seed=61)
+    x0 = I.make_features(w)
+    ps = [I.make_vig_params(w, l, bias=bias) for l in range(3)]
+    pd = [_dev_params(p) for p in ps]
+    _say("vig tail", label)
+    xs, us, graphs = _run_blocks(w, 3, to_dev(x0), pd)
+    for l in range(3):
+        ref = O.vig_block_ref(from_dev(xs[l]).value, graphs[l].cpu().numpy(), _host_params(ps[l]),
+                              **_grid(w))
+        check_close(from_dev(xs[l + 1]).value, ref, w.dtype, f"{label} block {l}")
+    la = api.Lookahead(torch.cuda.current_stream(), torch.cuda.Stream())
+    for sc in (api.GL_SCHED_LOOKAHEAD_FUSED, api.GL_SCHED_LOOKAHEAD):
+        out = la.vig_stack(xs[0], pd, [1, 2, 1], w.k, schedule=sc, **_grid(w))
+        torch.cuda.synchronize()
+        assert torch.equal(out, xs[-1]), (label, sc)
+    # standard schedule: the graph of each block's own U
+    x = xs[0]
+    for l, d in enumerate((1, 2, 1)):
+        u = api.linear(x, pd[l]["W_in"], pd[l].get("b_in"))
+        keys = api.pool_keys(u, H, W, r) if r > 1 else None
+        x, _ = la.vig_block(x, api.knn_graph(u, w.k, d, keys=keys), pd[l],
+                            api.vig_workspace(x, w.k, **_grid(w)), **_grid(w))
+    out = la.vig_stack(xs[0], pd, [1, 2, 1], w.k, schedule=api.GL_SCHED_STANDARD, **_grid(w))
+    torch.cuda.synchronize()
+    la.close()
+    assert torch.equal(out, x), (label, "standard")
