@@ -90,7 +90,11 @@ hipError_t launch_knn(const void* x, const void* keys, int B, int N, int C, int 
                       int dil, int dt_bf16, int32_t* idx_out, hipStream_t stream,
                       hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr);
 
-// Large key sets (M > 256) use the kernel that streams key chunks through LDS.
+hipError_t launch_knn_tile(const KnnArgs& a, int dt_bf16, hipStream_t stream, hipEvent_t ev0,
+                           hipEvent_t ev1);
+
+// Large key sets (M > 256) use the kernel that streams key chunks through LDS
+// (on small grids the in-register one: launch_knn).
 bool knn_use_stream(int M, int C, int dt_bf16);
 hipError_t launch_knn_stream(const KnnArgs& a, int dt_bf16, hipStream_t stream, hipEvent_t ev0,
                              hipEvent_t ev1);

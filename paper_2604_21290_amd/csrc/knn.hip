@@ -44,15 +44,10 @@ KnnArgs make_knn_args(const void* x, const void* keys, int B, int N, int C, int 
 
 int knn_list_regs(int KK) { return KK <= 16 ? 1 : KK <= 32 ? 2 : 4; }
 
-hipError_t launch_knn(const void* x, const void* keys, int B, int N, int C, int M, int k,
-                      int dil, int dt_bf16, int32_t* idx_out, hipStream_t stream,
-                      hipEvent_t ev0, hipEvent_t ev1) {
-  const KnnArgs a = make_knn_args(x, keys, B, N, C, M, k, dil, idx_out);
-  if (knn_use_stream(M, C, dt_bf16)) return launch_knn_stream(a, dt_bf16, stream, ev0, ev1);
-  if (knn_use_resident(B, N, M, C, dt_bf16)) return launch_knn_resident(a, stream, ev0, ev1);
-  if (knn_use_wide(M, C, dt_bf16)) return launch_knn_wide(a, stream, ev0, ev1);
-  const size_t smem = knn_smem_bytes(C, dt_bf16);
-  const dim3 grid(B * ((N + kKnnRows - 1) / kKnnRows)), block(kKnnThreads);
+hipError_t launch_knn_tile(const KnnArgs& a, int dt_bf16, hipStream_t stream, hipEvent_t ev0,
+                           hipEvent_t ev1) {
+  const size_t smem = knn_smem_bytes(a.C, dt_bf16);
+  const dim3 grid(a.B * ((a.N + kKnnRows - 1) / kKnnRows)), block(kKnnThreads);
   const int R = knn_list_regs(a.KK);
   const void* fn = nullptr;
   if (dt_bf16) {
@@ -63,6 +58,25 @@ hipError_t launch_knn(const void* x, const void* keys, int B, int N, int C, int 
                                                           : (const void*)&knn_kernel<0, 4>;
   }
   return launch_with_smem(fn, grid, block, smem, stream, ev0, ev1, a);
+}
+
+hipError_t launch_knn(const void* x, const void* keys, int B, int N, int C, int M, int k,
+                      int dil, int dt_bf16, int32_t* idx_out, hipStream_t stream,
+                      hipEvent_t ev0, hipEvent_t ev1) {
+  const KnnArgs a = make_knn_args(x, keys, B, N, C, M, k, dil, idx_out);
+  // Large key sets on small grids take the in-register kernel, which ranks the
+  // same packed keys.  A streamed workgroup lives for one wave's sweep of all
+  // keys, whatever the grid; here four waves share the sweep of 16 rows, so
+  // time grows with the workgroups instead.  us, streamed / in-register, k = 9,
+  // d = 2: 3 x 513, C = 204, fp32 89 / 27 (99 workgroups); bf16 1 x 3136, C = 96
+  // 106 / 41 (196), 12 x 1024, C = 200 69 / 48 (768), 32 x 513, C = 200 47.8 / 46.2
+  // (1056), 12 x 2048, C = 200 126 / 176 (1536), 32 x 1024, C = 96 54 / 59 (2048).
+  if (knn_use_stream(M, C, dt_bf16) && (long long)B * ((N + kKnnRows - 1) / kKnnRows) <= 1024)
+    return launch_knn_tile(a, dt_bf16, stream, ev0, ev1);
+  if (knn_use_stream(M, C, dt_bf16)) return launch_knn_stream(a, dt_bf16, stream, ev0, ev1);
+  if (knn_use_resident(B, N, M, C, dt_bf16)) return launch_knn_resident(a, stream, ev0, ev1);
+  if (knn_use_wide(M, C, dt_bf16)) return launch_knn_wide(a, stream, ev0, ev1);
+  return launch_knn_tile(a, dt_bf16, stream, ev0, ev1);
 }
 
 }  // namespace gl

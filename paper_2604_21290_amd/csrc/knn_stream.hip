@@ -530,8 +530,9 @@ int knn_stream_ks(int C, int dt_bf16) {
   return 0;
 }
 
-// Large key sets.  (For many query rows against a small key set, e.g. 3136
-// rows x 196 pooled keys, the in-register kernel measured faster.)
+// Large key sets, on grids past 1024 tiles of 16 rows (launch_knn).  (For many
+// query rows against a small key set, e.g. 3136 rows x 196 pooled keys, the
+// in-register kernel measured faster.)
 bool knn_use_stream(int M, int C, int dt_bf16) {
   return M > 256 && knn_stream_ks(C, dt_bf16) > 0;
 }

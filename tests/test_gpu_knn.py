@@ -267,3 +267,40 @@ def test_nearest_keys_in_one_lane(case):
     check_idx(got, O.knn_distances(xs.value, ks.value, rows=rows), k, d, rows=rows, label=label)
     near = min(len(lane), k * d)
     assert (got[:, :, :(near + d - 1) // d] % 16 == 5).all(), label
+
+
+# -- large key sets: the streamed kernel and, on small grids, the in-register one ------
+TWO_KERNELS = [
+    # label, B, N, C, k, d, dtype; B images are streamed, one is not
+    ("two_steps", 26, 641, 40, 9, 2, I.BF16),
+    ("three_steps_k16", 12, 1400, 96, 16, 2, I.BF16),
+    ("four_steps_k64", 20, 830, 120, 16, 4, I.BF16),
+    ("six_steps", 33, 513, 192, 9, 3, I.BF16),
+    ("eight_steps", 40, 450, 248, 9, 1, I.BF16),
+    ("twelve_steps", 61, 269, 384, 9, 2, I.BF16),
+    ("twenty_steps", 30, 560, 640, 9, 1, I.BF16),
+    ("fp32_ragged", 33, 513, 36, 12, 3, I.F32),
+    ("fp32_wide", 65, 257, 204, 9, 1, I.F32),
+]
+
+
+@pytest.mark.parametrize("case", TWO_KERNELS, ids=[c[0] for c in TWO_KERNELS])
+def test_stream_and_tile_agree(case):
+    """The two kernels rank the same packed keys: a batch past 1024 tiles of 16
+    rows (streamed) and its first and last image alone (in-register) give the
+    same graph, which is the oracle's."""
+    require_gpu()
+    from paper_2604_21290_amd import api
+    label, B, N, C, k, d, dt = case
+    assert B * ((N + 15) // 16) > 1024 >= (N + 15) // 16
+    x = I.random_features(N + C, B, N, C, dt, unit=False)
+    xd = to_dev(x)
+    _say("stream and tile", label)
+    all_ = api.knn_graph(xd, k, d)
+    for b in (0, B - 1):
+        one = api.knn_graph(xd[b:b + 1].contiguous(), k, d)
+        torch.cuda.synchronize()
+        assert torch.equal(one[0], all_[b]), (label, b)
+    rows = np.unique(np.linspace(0, N - 1, 24).astype(int))
+    check_idx(all_[:1].cpu().numpy(), O.knn_distances(x.value[:1], rows=rows), k, d, rows=rows,
+              label=label)
