@@ -67,7 +67,7 @@ __device__ __forceinline__ void block_body(char* smem, const KnnArgs& ka, const 
     }
   } else {
     j = xcd_remap(j, nu);
-    mrconv_tile<DT, RT, KB, false, (WK > 0) && kBlockWideT3, false, false, ACT>(smem, ma, j * 16 * RT);
+    mrconv_tile<DT, RT, KB, false, (WK > 0) && kBlockWideT3, false, 0, ACT>(smem, ma, j * 16 * RT);
   }
 }
 

@@ -31,16 +31,16 @@ template <int DT, int RT, int KB, bool ACT = false>
 __global__ __launch_bounds__(kMrThreads) __attribute__((amdgpu_waves_per_eu(3, 8))) void mrconv_kernel(MrArgs a) {
   extern __shared__ __align__(16) char smem[];
   const int blk = xcd_remap(blockIdx.x, gridDim.x);
-  mrconv_tile<DT, RT, KB, false, false, false, false, ACT>(smem, a, blk * 16 * RT);
+  mrconv_tile<DT, RT, KB, false, false, false, 0, ACT>(smem, a, blk * 16 * RT);
 }
 
-// Narrow layers over many node tiles: one output tile per wave and pass and
-// one gather task per thread (78 VGPRs at k <= 9: six waves per SIMD).
-template <int DT, int RT, int KB, bool ACT = false>
-__global__ __launch_bounds__(kMrThreads) __attribute__((amdgpu_waves_per_eu(4, 8))) void mrconv_lean_kernel(MrArgs a) {
+// Narrow layers over many node tiles: NC output tiles per wave, the layer in one
+// pass, and one gather task per thread.
+template <int DT, int RT, int KB, int NC, bool ACT = false>
+__global__ __launch_bounds__(kMrThreads) __attribute__((amdgpu_waves_per_eu(RT * NC == 12 && ACT ? 3 : 4, 8))) void mrconv_lean_kernel(MrArgs a) {
   extern __shared__ __align__(16) char smem[];
   const int blk = xcd_remap(blockIdx.x, gridDim.x);
-  mrconv_tile<DT, RT, KB, false, false, false, true, ACT>(smem, a, blk * 16 * RT);
+  mrconv_tile<DT, RT, KB, false, false, false, NC, ACT>(smem, a, blk * 16 * RT);
 }
 
 // Small grids: workgroup blk computes output-column group blk % ncg (a.col_tiles
@@ -53,7 +53,7 @@ __global__ __launch_bounds__(kMrThreads) void mrconv_cols_kernel(MrArgs a) {
   const int ncg = (nct + a.col_tiles - 1) / a.col_tiles;
   const int blk = blockIdx.x, cg = blk % ncg;
   const int tile0 = cg * a.col_tiles;
-  mrconv_tile<DT, RT, KB, false, false, true, false, ACT>(smem, a, (blk / ncg) * 16 * RT, tile0,
+  mrconv_tile<DT, RT, KB, false, false, true, 0, ACT>(smem, a, (blk / ncg) * 16 * RT, tile0,
                                                           min(nct, tile0 + a.col_tiles));
 }
 
@@ -66,14 +66,14 @@ __global__ __launch_bounds__(kMrThreads) void mrconv_heads_kernel(MrArgs a) {
   mrconv_tile<DT, RT, KB, true>(smem, a, blk * 16 * RT);
 }
 
-template <int DT, int RT, bool HEADS = false, bool COLS = false, bool LEAN = false, bool ACT = false>
+template <int DT, int RT, bool HEADS = false, bool COLS = false, int LEAN = 0, bool ACT = false>
 const void* mrconv_fn_kb(int KB) {
-  if constexpr (LEAN) {
+  if constexpr (LEAN > 0) {
     switch (KB) {
-      case 9: return (const void*)&mrconv_lean_kernel<DT, RT, 9, ACT>;
-      case 16: return (const void*)&mrconv_lean_kernel<DT, RT, 16, ACT>;
-      case 32: return (const void*)&mrconv_lean_kernel<DT, RT, 32, ACT>;
-      default: return (const void*)&mrconv_lean_kernel<DT, RT, 64, ACT>;
+      case 9: return (const void*)&mrconv_lean_kernel<DT, RT, 9, LEAN, ACT>;
+      case 16: return (const void*)&mrconv_lean_kernel<DT, RT, 16, LEAN, ACT>;
+      case 32: return (const void*)&mrconv_lean_kernel<DT, RT, 32, LEAN, ACT>;
+      default: return (const void*)&mrconv_lean_kernel<DT, RT, 64, LEAN, ACT>;
     }
   } else if constexpr (COLS) {
     switch (KB) {
@@ -100,7 +100,7 @@ const void* mrconv_fn_kb(int KB) {
 }
 
 // The dense variants' table, with or without the GELU epilogue (a.act_out).
-template <int DT, int RT, bool COLS = false, bool LEAN = false>
+template <int DT, int RT, bool COLS = false, int LEAN = 0>
 const void* mrconv_fn_act(int KB, int act) {
   return act ? mrconv_fn_kb<DT, RT, false, COLS, LEAN, true>(KB)
              : mrconv_fn_kb<DT, RT, false, COLS, LEAN, false>(KB);
@@ -208,14 +208,17 @@ hipError_t launch_mrconv_args(const MrArgs& a0, int dt_bf16, int rt, void* split
     fn = dt_bf16 ? (rt == 2 ? mrconv_fn_kb<1, 2, true>(KB) : mrconv_fn_kb<1, 1, true>(KB))
                  : (rt == 2 ? mrconv_fn_kb<0, 2, true>(KB) : mrconv_fn_kb<0, 1, true>(KB));
   } else if (mrconv_use_lean(a.C, Cout, row_tiles)) {
-    // 64-node tiles when they fit 64 KB of LDS (measured 2-3 % faster than 32)
-    if (mrconv_smem_bytes(C, k, dt_bf16, 4) <= 65536) {
-      fn = dt_bf16 ? mrconv_fn_act<1, 4, false, true>(KB, act) : mrconv_fn_act<0, 4, false, true>(KB, act);
+    // 64-node tiles when they fit 64 KB of LDS (measured 2-3 % faster than 32),
+    // up to 192 columns (three output tiles per wave)
+    const int nc = nct <= 8 ? 2 : nct <= 12 ? 3 : 4;
+    if (nc < 4 && mrconv_smem_bytes(C, k, dt_bf16, 4) <= 65536) {
+      fn = dt_bf16 ? (nc == 2 ? mrconv_fn_act<1, 4, false, 2>(KB, act) : mrconv_fn_act<1, 4, false, 3>(KB, act))
+                   : (nc == 2 ? mrconv_fn_act<0, 4, false, 2>(KB, act) : mrconv_fn_act<0, 4, false, 3>(KB, act));
       return launch_with_smem(fn, dim3((a.R + 63) / 64), block, mrconv_smem_bytes(C, k, dt_bf16, 4),
                               stream, ev0, ev1, a);
     }
-    fn = dt_bf16 ? (rt == 2 ? mrconv_fn_act<1, 2, false, true>(KB, act) : mrconv_fn_act<1, 1, false, true>(KB, act))
-                 : (rt == 2 ? mrconv_fn_act<0, 2, false, true>(KB, act) : mrconv_fn_act<0, 1, false, true>(KB, act));
+    fn = dt_bf16 ? (rt == 2 ? mrconv_fn_act<1, 2, false, 4>(KB, act) : mrconv_fn_act<1, 1, false, 4>(KB, act))
+                 : (rt == 2 ? mrconv_fn_act<0, 2, false, 4>(KB, act) : mrconv_fn_act<0, 1, false, 4>(KB, act));
   } else {
     fn = dt_bf16 ? (rt == 2 ? mrconv_fn_act<1, 2>(KB, act) : mrconv_fn_act<1, 1>(KB, act))
                  : (rt == 2 ? mrconv_fn_act<0, 2>(KB, act) : mrconv_fn_act<0, 1>(KB, act));

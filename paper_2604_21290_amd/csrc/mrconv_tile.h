@@ -62,15 +62,15 @@ __device__ __forceinline__ bool mr_step_needed(const MrArgs& a, int n0, int s, i
 // COLS: only output tiles tile0 .. tile_end-1 (a column group of a small grid),
 // one tile per wave and pass, with the W operands of kMrKUCols k-steps per batch.
 constexpr int kMrKUCols = 12;
-// LEAN: one output tile per wave and pass and one gather task per thread and
-// round, for layers of few output tiles that run many node tiles: the
-// registers saved buy more waves per SIMD.
-template <bool COLS, bool LEAN = false> struct MrBatch {
-  static constexpr int KU = COLS ? kMrKUCols : kMrKU;   // k-steps per batch of W operands
-  static constexpr int NC = COLS || LEAN ? 1 : 4;       // output tiles per wave and pass
+// LEAN > 0: that many output tiles per wave, which take the layer in one pass, and
+// one gather task per thread and round, for layers of few output tiles that run
+// many node tiles: the registers saved buy more waves per SIMD.
+template <bool COLS, int LEAN = 0> struct MrBatch {
+  static constexpr int KU = COLS ? kMrKUCols : LEAN > 2 ? 2 : kMrKU;  // k-steps per batch of W operands
+  static constexpr int NC = COLS ? 1 : LEAN ? LEAN : 4;    // output tiles per wave and pass
 };
 
-template <int DT, bool HEADS, bool COLS = false, bool LEAN = false>
+template <int DT, bool HEADS, bool COLS = false, int LEAN = 0>
 __device__ __forceinline__ void mr_load_w(uint4 (&bw)[(MrBatch<COLS, LEAN>::KU)][(MrBatch<COLS, LEAN>::NC)],
                                           const MrArgs& a, const char* Wb, int w, int p, int s0,
                                           int K2, int Cout, int g, int t, int tile0 = 0,
@@ -92,6 +92,26 @@ __device__ __forceinline__ void mr_load_w(uint4 (&bw)[(MrBatch<COLS, LEAN>::KU)]
   }
 }
 
+// Maximum of the bf16 pairs in two words.  gfx950 has no packed bf16 maximum, but
+// a bf16 below 2^121 in magnitude is, bit for bit, a finite fp16 number, and both
+// orders are the order of sign and magnitude; so v_pk_maximum3_f16 takes the
+// maximum of three words' pairs in one instruction, against four unpacks and
+// three-input maxima.  The other values (NaN and infinities among them) have an
+// fp16 exponent of all ones, which the IEEE maximum either keeps as NaN or
+// keeps as the largest: any that could matter shows in the result
+// (bf16_pair_unsafe), which is then taken in fp32.
+typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ uint32_t max_bf16_pair(uint32_t a, uint32_t b) {
+  return __builtin_bit_cast(uint32_t, __builtin_elementwise_maximum(__builtin_bit_cast(f16x2, a),
+                                                                    __builtin_bit_cast(f16x2, b)));
+}
+// below every pair that is safe, and unsafe itself (fp16 -inf)
+constexpr uint32_t kBf16PairLowest = 0xfc00fc00u;
+// the sign bits of the halves whose fp16 exponent is all ones
+__device__ __forceinline__ uint32_t bf16_pair_unsafe(uint32_t w) {
+  return ((w & 0x7c007c00u) + 0x04000400u) & 0x80008000u;
+}
+
 // Gather-max of TM nodes from flattened node row0 (Eq. 2): row r of dst
 // (dst + r * dst_stride, LDS or global memory) receives [x_i | m_i] with
 // m_i = max_t keys[idx[i, t]] - x_i.  sIdx holds the TM x k neighbour lists,
@@ -100,7 +120,7 @@ __device__ __forceinline__ void mr_load_w(uint4 (&bw)[(MrBatch<COLS, LEAN>::KU)]
 // written.  Called by all 256 threads.
 // T3: three tasks per thread in flight instead of two (a caller with registers
 // to spare takes the 32-node tile's 768 tasks of C = 192 in one round).
-template <int DT, int KB, bool T3 = false, bool LEAN = false>
+template <int DT, int KB, bool T3 = false, int LEAN = 0>
 __device__ __forceinline__ void mr_gather_rows(const MrArgs& a, int row0, int TM,
                                                const int32_t* sIdx, char* dst, size_t dst_stride) {
   constexpr int ES = DT ? 2 : 4;
@@ -113,23 +133,42 @@ __device__ __forceinline__ void mr_gather_rows(const MrArgs& a, int row0, int TM
   constexpr int KG = KB < 16 ? KB : 16;    // neighbour loads in flight per group
   constexpr int TPT = KB <= 9 && !LEAN ? (T3 ? 3 : 2) : 1;  // tasks per thread per iteration
   const int ntask = TM * CG;
+  // Task e is vector e % CG of node e / CG; a thread's tasks are kMrThreads apart,
+  // so (node, vector) advance by a fixed step and one carry.  The tile's nodes
+  // lie in image b0 or, when an image has at least TM nodes, the next one.
+  const int b0 = row0 / N, row1 = (b0 + 1) * N;
+  const bool one_edge = N >= TM;
+  const int dr = kMrThreads / CG, dc = kMrThreads - dr * CG;
+  int tr = tid / CG, tc = tid - tr * CG;
   for (int e0 = tid; e0 < ntask; e0 += TPT * kMrThreads) {
+    int nr[TPT], nc[TPT];
     float mx[TPT][VEC];
+    uint32_t mp[TPT][4];  // bf16: the maxima as stored pairs
     uint4 xraw[TPT];
     const char* kbase[TPT];
     const int32_t* nb[TPT];
 #pragma unroll
     for (int q = 0; q < TPT; ++q) {
-      const int e = min(e0 + q * kMrThreads, ntask - 1);
-      const int r = e / CG, cg = e - r * CG;
+      // past the last task: the last node's rows again (not written)
+      const int r = min(tr, TM - 1), cg = tc;
+      nr[q] = tr;
+      nc[q] = tc;
+      tr += dr;
+      tc += dc;
+      if (tc >= CG) {
+        tc -= CG;
+        ++tr;
+      }
       const int row = min(row0 + r, R - 1);
-      const int b = row / N;
+      const int b = one_edge ? b0 + (row >= row1) : row / N;
       xraw[q] = *reinterpret_cast<const uint4*>(static_cast<const char*>(a.x) +
                                                 ((size_t)row * C + cg * VEC) * ES);
       kbase[q] = static_cast<const char*>(a.keys) + ((size_t)b * M * C + cg * VEC) * ES;
       nb[q] = sIdx + r * k;
 #pragma unroll
       for (int i = 0; i < VEC; ++i) mx[q][i] = -INFINITY;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) mp[q][i] = kBf16PairLowest;
     }
 #pragma unroll 1
     for (int t0 = 0; t0 < KB; t0 += KG) {
@@ -146,18 +185,45 @@ __device__ __forceinline__ void mr_gather_rows(const MrArgs& a, int row0, int TM
       for (int q = 0; q < TPT; ++q)
 #pragma unroll
         for (int u = 0; u < KG; ++u) {
-          float kf[VEC];
-          if (DT) unpack_bf16x8(raw[q][u], kf);
-          else { const float4 v = __builtin_bit_cast(float4, raw[q][u]); kf[0] = v.x; kf[1] = v.y; kf[2] = v.z; kf[3] = v.w; }
+          if constexpr (DT) {
+            const u32x4 v = __builtin_bit_cast(u32x4, raw[q][u]);
 #pragma unroll
-          for (int i = 0; i < VEC; ++i) mx[q][i] = fmaxf(mx[q][i], kf[i]);
+            for (int i = 0; i < 4; ++i)
+              mp[q][i] = KB == KG && u == 0 ? v[i] : max_bf16_pair(mp[q][i], v[i]);
+          } else {
+            const f32x4 v = __builtin_bit_cast(f32x4, raw[q][u]);
+#pragma unroll
+            for (int i = 0; i < VEC; ++i) mx[q][i] = fmaxf(mx[q][i], v[i]);
+          }
         }
+    }
+    if constexpr (DT) {
+      uint32_t unsafe = 0;
+#pragma unroll
+      for (int q = 0; q < TPT; ++q)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) unsafe |= bf16_pair_unsafe(mp[q][i]);
+      if (__any(unsafe != 0)) {  // rare: infinities, NaN, or magnitudes from 2^121 on
+#pragma unroll
+        for (int q = 0; q < TPT; ++q) {
+#pragma unroll 1
+          for (int tt = 0; tt < k; ++tt) {
+            float kf[VEC];
+            unpack_bf16x8(*reinterpret_cast<const uint4*>(kbase[q] + ((size_t)(uint32_t)nb[q][tt] << 4)), kf);
+#pragma unroll
+            for (int i = 0; i < VEC; ++i) mx[q][i] = fmaxf(mx[q][i], kf[i]);
+          }
+          const uint4 p = pack_bf16x8(mx[q]);  // a maximum of stored values: exact
+          mp[q][0] = p.x; mp[q][1] = p.y; mp[q][2] = p.z; mp[q][3] = p.w;
+        }
+      }
     }
 #pragma unroll
     for (int q = 0; q < TPT; ++q) {
       const int e = e0 + q * kMrThreads;
       if (e >= ntask) continue;
-      const int r = e / CG, cg = e - r * CG;
+      const int r = nr[q], cg = nc[q];
+      if constexpr (DT) unpack_bf16x8(make_uint4(mp[q][0], mp[q][1], mp[q][2], mp[q][3]), mx[q]);
       float xf[VEC];
       if (DT) unpack_bf16x8(xraw[q], xf);
       else { const float4 v = __builtin_bit_cast(float4, xraw[q]); xf[0] = v.x; xf[1] = v.y; xf[2] = v.z; xf[3] = v.w; }
@@ -199,7 +265,7 @@ __device__ __forceinline__ void mr_gather_tile(const MrArgs& a, int blk, int TM,
 // ACT: GELU on each output before its rounding (a.act_out; compiled in only
 // for the full block's update, so the other updates carry none of its code).
 template <int DT, int RT, int KB, bool HEADS = false, bool T3 = false, bool COLS = false,
-          bool LEAN = false, bool ACT = false>
+          int LEAN = 0, bool ACT = false>
 __device__ __forceinline__ void mrconv_tile(char* smem, const MrArgs& a, int row0, int tile0 = 0,
                                             int tile_end = 0) {
   constexpr int TM = 16 * RT;
@@ -244,7 +310,8 @@ __device__ __forceinline__ void mrconv_tile(char* smem, const MrArgs& a, int row
   // batch is multiplied, so no batch after the first waits on its own loads.
   constexpr bool PIPE = T3 && !HEADS && !COLS && !LEAN;
   uint4 bw2[KU][NC] = {};
-  for (int p = 0; T0 + w + 4 * NC * p < TE; ++p) {
+  // (the lean tile is one pass, which every wave takes: its epilogue has barriers)
+  for (int p = 0; LEAN > 0 ? p == 0 : T0 + w + 4 * NC * p < TE; ++p) {
     f32x4 acc[RT][NC];
 #pragma unroll
     for (int rt = 0; rt < RT; ++rt)
@@ -274,14 +341,14 @@ __device__ __forceinline__ void mrconv_tile(char* smem, const MrArgs& a, int row
 #pragma unroll
           for (int rt = 0; rt < RT; ++rt) {
             if (DT) {
-              acc[rt][c4] = mfma_bf16(af[rt], bv, acc[rt][c4]);
+              acc[rt][c4] = LEAN ? mfma_bf16(bv, af[rt], acc[rt][c4]) : mfma_bf16(af[rt], bv, acc[rt][c4]);
             } else {
               const float4 x4 = __builtin_bit_cast(float4, af[rt]);
               const float4 w4 = __builtin_bit_cast(float4, bv);
-              acc[rt][c4] = mfma_f32(x4.x, w4.x, acc[rt][c4]);
-              acc[rt][c4] = mfma_f32(x4.y, w4.y, acc[rt][c4]);
-              acc[rt][c4] = mfma_f32(x4.z, w4.z, acc[rt][c4]);
-              acc[rt][c4] = mfma_f32(x4.w, w4.w, acc[rt][c4]);
+              acc[rt][c4] = LEAN ? mfma_f32(w4.x, x4.x, acc[rt][c4]) : mfma_f32(x4.x, w4.x, acc[rt][c4]);
+              acc[rt][c4] = LEAN ? mfma_f32(w4.y, x4.y, acc[rt][c4]) : mfma_f32(x4.y, w4.y, acc[rt][c4]);
+              acc[rt][c4] = LEAN ? mfma_f32(w4.z, x4.z, acc[rt][c4]) : mfma_f32(x4.z, w4.z, acc[rt][c4]);
+              acc[rt][c4] = LEAN ? mfma_f32(w4.w, x4.w, acc[rt][c4]) : mfma_f32(x4.w, w4.w, acc[rt][c4]);
             }
           }
         }
@@ -307,7 +374,82 @@ __device__ __forceinline__ void mrconv_tile(char* smem, const MrArgs& a, int row
         batch(bw, s0);
       }
     }
-    // -- epilogue: + bias, [GELU], round once, store -----------------------------
+    // -- epilogue: + bias, [GELU], round once, store --------------------------------
+    if constexpr (LEAN > 0) {
+    // The lean tile's operands were swapped (W first), so lane (g, t) holds
+    // columns n .. n+3 of node 16 rt + t.  The layer is one pass: its rows go
+    // into the A-tile, when they fit there, and are stored whole, 16 bytes a lane
+    // (C = 160, 25088 nodes: 17.5 -> 15.8 us against 2-byte stores; the two
+    // barriers cost the other tiles more than that gains); else four columns a
+    // lane, or one where a row is not a multiple of four.
+    const bool rows = Cout <= 2 * C && (Cout * ES & 15) == 0;  // uniform
+    if (rows) __syncthreads();  // every wave is done with the A-tile
+#pragma unroll
+    for (int c4 = 0; c4 < NC; ++c4) {
+      if (!nvalid[c4]) continue;  // wave-uniform
+      const int n = (T0 + w + 4 * (NC * p + c4)) * 16 + 4 * g;
+      float bn[4];
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        bn[v] = 0.f;
+        if (a.bias) {
+          const int nc = min(n + v, Cout - 1);
+          bn[v] = DT ? bf16_bits_to_f32(static_cast<const uint16_t*>(a.bias)[nc])
+                     : static_cast<const float*>(a.bias)[nc];
+        }
+      }
+#pragma unroll
+      for (int rt = 0; rt < RT; ++rt) {
+        float y[4];
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          y[v] = acc[rt][c4][v] + bn[v];
+          if constexpr (ACT) y[v] = gelu_f32(y[v]);
+        }
+        const uint2 y2 = make_uint2(f32x2_to_bf16x2_bits(y[0], y[1]), f32x2_to_bf16x2_bits(y[2], y[3]));
+        const int r = rt * 16 + t, row = row0 + r;
+        if (rows) {
+          char* d = sA + r * lds_row + n * ES;
+          if (n < Cout) {
+            if (DT) *reinterpret_cast<uint2*>(d) = y2;
+            else *reinterpret_cast<float4*>(d) = make_float4(y[0], y[1], y[2], y[3]);
+          }
+        } else if (row < R) {
+          const size_t o = (size_t)row * Cout + n;
+          if ((Cout & 3) == 0) {
+            if (n < Cout) {
+              if (DT) *reinterpret_cast<uint2*>(static_cast<uint16_t*>(a.out) + o) = y2;
+              else *reinterpret_cast<float4*>(static_cast<float*>(a.out) + o) = make_float4(y[0], y[1], y[2], y[3]);
+            }
+          } else {
+#pragma unroll
+            for (int v = 0; v < 4; ++v)
+              if (n + v < Cout) {
+                if (DT) static_cast<uint16_t*>(a.out)[o + v] = (uint16_t)f32_to_bf16_bits(y[v]);
+                else static_cast<float*>(a.out)[o + v] = y[v];
+              }
+          }
+        }
+      }
+    }
+    if (rows) {
+      __syncthreads();
+      // the tile's rows are contiguous in out
+      const int vr = Cout * ES / 16, nv = min(TM, R - row0) * vr;
+      char* d = static_cast<char*>(a.out) + (size_t)row0 * Cout * ES;
+      const int er = kMrThreads / vr, ec = kMrThreads - er * vr;
+      int r = tid / vr, c = tid - r * vr;
+      for (int e = tid; e < nv; e += kMrThreads) {
+        *reinterpret_cast<uint4*>(d + (size_t)e * 16) = *reinterpret_cast<const uint4*>(sA + r * lds_row + c * 16);
+        r += er;
+        c += ec;
+        if (c >= vr) {
+          c -= vr;
+          ++r;
+        }
+      }
+    }
+    } else {
     // a full tile (all TM nodes below R, Cout a multiple of 16; uniform)
     // stores without per-lane guards
     const bool full = row0 + TM <= R && (Cout & 15) == 0;
@@ -340,6 +482,7 @@ __device__ __forceinline__ void mrconv_tile(char* smem, const MrArgs& a, int row
           for (int v = 0; v < 4; ++v)
             if (n < Cout && row0 + rt * 16 + 4 * g + v < R) put(rt, v);
       }
+    }
     }
   }
 }

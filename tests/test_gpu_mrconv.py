@@ -198,3 +198,66 @@ def test_mrconv_heads(case):
                            return_concat=True)
     check_close(from_dev(out).value, ref, w.dtype, label,
                 mag=mrconv_mag(xcat, _block_diag(Wh.value)), n_terms=2 * w.C)
+
+
+# -- the gather's packed maximum ------------------------------------------------------
+PACKED = [
+    # label, B, N, C, k, Cout (the kernel: column groups, fused, lean, two-pass), dtype
+    ("cols_tiny_images", 7, 9, 40, 3, 96, I.BF16),
+    ("fused_k20", 24, 130, 272, 20, 272, I.BF16),
+    ("lean_ragged", 40, 251, 72, 9, 72, I.BF16),
+    ("lean_k40", 35, 300, 40, 40, 48, I.BF16),
+    # the lean tile's stores: wider than its LDS rows, rows of no multiple of four or
+    # eight columns, three and four tiles a wave, waves with none
+    ("lean_wide_out", 33, 260, 40, 4, 104, I.BF16),
+    ("lean_cout_37", 33, 260, 40, 5, 37, I.BF16),
+    ("lean_cout_20", 33, 260, 40, 9, 20, I.BF16),
+    ("lean_three_tiles", 33, 260, 168, 16, 168, I.BF16),
+    ("lean_four_tiles", 33, 260, 136, 9, 200, I.BF16),
+    ("lean_fp32", 33, 260, 68, 9, 68, I.F32),
+    ("two_pass", 2, 150, 640, 9, 648, I.BF16),
+    ("fp32", 3, 77, 36, 9, 40, I.F32),
+]
+
+
+@pytest.mark.parametrize("case", PACKED, ids=[c[0] for c in PACKED])
+def test_gather_edge_values(case):
+    """Neighbours whose maximum is an infinity, a value around 2^121 (where the
+    packed maximum hands over to fp32), a signed zero, the smallest magnitudes
+    or equal in the upper bits only.  W picks m's channels, so each output is
+    max_t x_j - x_i of one channel, rounded once: compared bit for bit with the
+    definition on the stored values, special values included."""
+    require_gpu()
+    from paper_2604_21290_amd import api
+    label, B, N, C, k, Co, dt = case
+    g = np.random.default_rng(N + k)
+    v = g.standard_normal((B, N, C)).astype(np.float32)
+    special = np.array([2.0 ** 121, 2.0 ** 120 * 1.9921875, 2.0 ** 126, 65504.0, 0.0, -0.0, 1e-38,
+                        -1e-38, 1e-40, -(2.0 ** 121), -(2.0 ** 122), -(2.0 ** 126)], dtype=np.float32)
+    hit = g.random((B, N, C)) < 0.15
+    v[hit] = g.choice(special, hit.sum())
+    v[:, 1::5] = special[g.integers(9, 12, (B, len(range(1, N, 5)), C))]  # whole rows far below
+    inf = g.random((B, N, C)) < 0.02 / C
+    v[inf] = g.choice(np.array([np.inf, -np.inf], dtype=np.float32), inf.sum())
+    x = torch.from_numpy(v).to(torch.bfloat16 if dt == I.BF16 else torch.float32)
+    idx = torch.from_numpy(I.random_indices(N, B, N, k, N))
+    idx[:, ::3] = idx[:, ::3] // 5 * 5 + 1                     # neighbours of those rows only
+    idx.clamp_(max=N - 1)
+    xf = x.float()
+    nb = torch.gather(xf[:, :, None, :].expand(-1, -1, k, -1).reshape(B, N * k, C), 1,
+                      (idx.long() * k).reshape(B, N * k, 1).expand(-1, -1, C)).reshape(B, N, k, C)
+    m = (nb.amax(2) - xf).to(x.dtype)                          # one rounding, as stored
+    W = torch.zeros((Co, 2 * C), dtype=x.dtype)
+    pick = torch.from_numpy(g.integers(0, C, Co))
+    W[torch.arange(Co), C + pick] = 1.0
+    print("[gpu-test] gather edge values", label, flush=True)
+    out = api.mrconv(x.cuda(), idx.cuda(), W.cuda())
+    torch.cuda.synchronize()
+    out = out.cpu().float()
+    want = m.float()[:, :, pick].clone()
+    # an infinity in another channel of the row meets a zero weight: NaN
+    bad = (~torch.isfinite(m.float())).sum(-1, keepdim=True) + (~torch.isfinite(xf)).sum(-1, keepdim=True)
+    want[bad - (~torch.isfinite(want)).int() > 0] = float("nan")
+    assert torch.equal(torch.isnan(out), torch.isnan(want)), label
+    assert torch.equal(out.nan_to_num(1.0, 2.0, 3.0), want.nan_to_num(1.0, 2.0, 3.0)), label
+    assert torch.isfinite(out).all(-1).float().mean() > 0.5
