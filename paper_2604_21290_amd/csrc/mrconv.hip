@@ -188,9 +188,7 @@ hipError_t launch_mrconv_args(const MrArgs& a0, int dt_bf16, int rt, void* split
     if (e != hipSuccess) return e;
     return launch_mrconv_gemm(a, dt_bf16, split_ws, stream, nullptr, ev1);
   }
-  const int TM = 16 * rt;
-  const size_t smem = mrconv_smem_bytes(C, k, dt_bf16, rt);
-  const int row_tiles = (a.R + TM - 1) / TM;
+  const int row_tiles = (a.R + 16 * rt - 1) / (16 * rt);
   // A grid of a few node tiles (a single image) leaves most CUs idle while each
   // workgroup streams all of W in batches; there the output columns are split
   // into groups of four 16-column tiles (one per wave), each group its own
@@ -198,7 +196,13 @@ hipError_t launch_mrconv_args(const MrArgs& a0, int dt_bf16, int rt, void* split
   const int nct = (Cout + 15) >> 4;
   a.col_tiles = a.heads <= 1 ? mrconv_col_tiles(a.R, Cout, rt) : 0;
   const int ncg = a.col_tiles ? (nct + a.col_tiles - 1) / a.col_tiles : 1;
-  const dim3 grid(row_tiles * ncg), block(kMrThreads);
+  // ... and, while two workgroups per CU hold them all, tiles of 16 nodes: half
+  // the gather and half the product in each workgroup's chain.  us, 32 / 16 nodes:
+  // one image of 196 nodes, C = 192, fp32 12.1 / 8.5, bf16 6.9 / 6.1; 3 x 513,
+  // C = 204, k = 12, fp32 19.2 / 15.8; 2048 nodes, C = 96, fp32 7.3 / 6.2.
+  if (a.col_tiles && rt == 2 && 2 * row_tiles * ncg <= 512) rt = 1;
+  const size_t smem = mrconv_smem_bytes(C, k, dt_bf16, rt);
+  const dim3 grid((a.R + 16 * rt - 1) / (16 * rt) * ncg), block(kMrThreads);
   const void* fn;
   const int act = a.act_out;
   if (a.col_tiles > 0) {

@@ -120,7 +120,7 @@ __device__ __forceinline__ uint32_t bf16_pair_unsafe(uint32_t w) {
 // written.  Called by all 256 threads.
 // T3: three tasks per thread in flight instead of two (a caller with registers
 // to spare takes the 32-node tile's 768 tasks of C = 192 in one round).
-template <int DT, int KB, bool T3 = false, int LEAN = 0>
+template <int DT, int KB, bool T3 = false, int LEAN = 0, bool COLS = false>
 __device__ __forceinline__ void mr_gather_rows(const MrArgs& a, int row0, int TM,
                                                const int32_t* sIdx, char* dst, size_t dst_stride) {
   constexpr int ES = DT ? 2 : 4;
@@ -131,7 +131,10 @@ __device__ __forceinline__ void mr_gather_rows(const MrArgs& a, int row0, int TM
   // Each task is one (node, 16-byte channel vector); with a small neighbour
   // bucket two tasks keep their loads in flight together.
   constexpr int KG = KB < 16 ? KB : 16;    // neighbour loads in flight per group
-  constexpr int TPT = KB <= 9 && !LEAN ? (T3 ? 3 : 2) : 1;  // tasks per thread per iteration
+  // tasks per thread per iteration (a small grid's workgroups, about two per CU,
+  // have the registers for three of nine loads; of sixteen, two or three are
+  // slower: 3 x 513, C = 204, k = 12, fp32 15.8 -> 25.1 us)
+  constexpr int TPT = COLS ? (KB <= 9 ? 3 : 1) : KB <= 9 && !LEAN ? (T3 ? 3 : 2) : 1;
   const int ntask = TM * CG;
   // Task e is vector e % CG of node e / CG; a thread's tasks are kMrThreads apart,
   // so (node, vector) advance by a fixed step and one carry.  The tile's nodes
@@ -301,7 +304,7 @@ __device__ __forceinline__ void mrconv_tile(char* smem, const MrArgs& a, int row
   if (T0 + w < TE) mr_load_w<DT, HEADS, COLS, LEAN>(bw, a, Wb, w, 0, 0, K2, Cout, g, t, tile0, tile_end);
   __syncthreads();
 
-  mr_gather_rows<DT, KB, T3, LEAN>(a, row0, TM, sIdx, sA, lds_row);
+  mr_gather_rows<DT, KB, T3, LEAN, COLS>(a, row0, TM, sIdx, sA, lds_row);
   __syncthreads();
 
   // -- FC on MFMA -----------------------------------------------------------------

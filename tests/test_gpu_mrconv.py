@@ -261,3 +261,26 @@ def test_gather_edge_values(case):
     assert torch.equal(torch.isnan(out), torch.isnan(want)), label
     assert torch.equal(out.nan_to_num(1.0, 2.0, 3.0), want.nan_to_num(1.0, 2.0, 3.0)), label
     assert torch.isfinite(out).all(-1).float().mean() > 0.5
+
+
+@pytest.mark.parametrize("B,N,C,k,Co,dt", [
+    (1, 17, 40, 9, 80, I.BF16),        # two tiles of 16 nodes, one of them one node
+    (3, 27, 136, 12, 136, I.F32),      # tiles across images
+    (1, 2048, 96, 9, 200, I.BF16),     # the most nodes of column groups, in 16-node tiles
+    (1, 2047, 72, 9, 640, I.BF16),     # ... too many groups for 16: 32-node tiles
+    (5, 100, 320, 9, 328, I.F32),      # wide fp32 rows: 16 nodes by LDS
+])
+def test_column_groups_edges(B, N, C, k, Co, dt):
+    """Small grids, whose output columns are split over workgroups, in tiles of 16
+    and of 32 nodes, against the oracle."""
+    require_gpu()
+    from paper_2604_21290_amd import api
+    x = I.random_features(B * N + C, B, N, C, dt, unit=False)
+    W = I.random_weight(C + Co, Co, C, dt)
+    idx = I.random_indices(N + k, B, N, k, N)
+    print("[gpu-test] column groups", B, N, C, k, Co, dt, flush=True)
+    out = api.mrconv(to_dev(x), torch.from_numpy(idx).cuda(), to_dev(W))
+    torch.cuda.synchronize()
+    ref, xcat = O.mrconv_ref(x.value, idx, W.value, return_concat=True)
+    check_close(from_dev(out).value, ref, dt, "column groups", mag=mrconv_mag(xcat, W.value),
+                n_terms=2 * C)
