@@ -47,7 +47,8 @@ struct DmaCfg {
   static_assert(kStage % (1024 * kWaves) == 0 && (STEP == 128 || STEP == 256), "whole loads per wave");
 };
 
-template <class G, int ACT_OUT, bool RES>
+// HALVES: the contraction's halves come from a.A and a.A2 (no residual).
+template <class G, int ACT_OUT, bool RES, bool HALVES = false>
 __global__ __launch_bounds__(G::kThreads) __attribute__((amdgpu_waves_per_eu(4, 8))) void gemm_dma_kernel(GemmArgs a) {
   extern __shared__ __align__(16) char smem[];
   constexpr int BM = G::BM, BN = G::BN, STEP = G::STEP, TM = G::TM, TN = G::TN, NL = G::kLoads;
@@ -73,16 +74,19 @@ __global__ __launch_bounds__(G::kThreads) __attribute__((amdgpu_waves_per_eu(4, 
   for (int i = 0; i < NL; ++i) {
     const int r = RPL * (w + G::kWaves * i) + lane / SPR;
     slot[i] = ((lane % SPR) ^ (r & (SPR - 1))) * 16;
-    src[i] = (r < BM ? static_cast<const char*>(a.A) + (size_t)min(m0 + r, R - 1) * rowb
+    src[i] = (r < BM ? static_cast<const char*>(a.A) + (size_t)min(m0 + r, R - 1) * (HALVES ? rowb >> 1 : rowb)
                      : static_cast<const char*>(a.W) + (size_t)min(n0 + r - BM, Cout - 1) * rowb) +
              slot[i];
   }
+  // from a row of A to the same place of the contraction in A2's row
+  const ptrdiff_t half = HALVES ? static_cast<const char*>(a.A2) - static_cast<const char*>(a.A) - (rowb >> 1) : 0;
   auto stage = [&](int s) {
     const int off = s * STEP;
     const uint32_t d = lds0 + (s & 1) * G::kStage + w * 1024;
 #pragma unroll
     for (int i = 0; i < NL; ++i) {
       const char* p = src[i] + off;
+      if (HALVES && RPL * (w + G::kWaves * i) < BM && off + slot[i] >= rowb >> 1) p += half;
       if (off + STEP > rowb)  // uniform: the last, partial stage
         p = off + slot[i] < rowb ? p : reinterpret_cast<const char*>(kZero16);
       lds_dma16(p, d + G::kWaves * i * 1024);
@@ -189,7 +193,10 @@ __global__ __launch_bounds__(G::kThreads) __attribute__((amdgpu_waves_per_eu(4, 
 
 template <class G>
 hipError_t launch_cfg(const GemmArgs& a, hipStream_t stream, hipEvent_t ev0, hipEvent_t ev1) {
-  const void* fn = a.act_out ? (a.residual ? (const void*)&gemm_dma_kernel<G, 1, true>
+  if (a.A2 && a.residual) return hipErrorInvalidValue;
+  const void* fn = a.A2 ? (a.act_out ? (const void*)&gemm_dma_kernel<G, 1, false, true>
+                                     : (const void*)&gemm_dma_kernel<G, 0, false, true>)
+                   : a.act_out ? (a.residual ? (const void*)&gemm_dma_kernel<G, 1, true>
                                            : (const void*)&gemm_dma_kernel<G, 1, false>)
                              : (a.residual ? (const void*)&gemm_dma_kernel<G, 0, true>
                                            : (const void*)&gemm_dma_kernel<G, 0, false>);

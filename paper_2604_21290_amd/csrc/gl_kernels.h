@@ -43,6 +43,8 @@ struct GemmArgs {
   void* out;             // [R, Cout]
   int R, K, Cout;
   int act_in, act_out;   // 0 none, 1 GELU (on A's elements / on the pre-residual output)
+  const void* A2 = nullptr;  // if given (bf16, no residual, K / 2 a multiple of 8): A and
+                             // A2 are [R, K / 2], the two halves of the contraction
 };
 
 // The row-local tail of a full ViG block (bf16): FC2 + residual, the FFN +
@@ -121,7 +123,8 @@ int mrconv_row_tiles(int C, int k, int dt_bf16, size_t lds_limit);
 int mrconv_k_bucket(int k);
 // MRConv.  Narrow channels: one fused kernel (gather into the LDS A-tile,
 // FC from it).  Wide channels (mrconv_use_split): a gather kernel writes
-// [x | m] to split_ws (mrconv_split_ws_bytes), then the tiled GEMM.
+// [x | m] rows (bf16: m rows) to split_ws (mrconv_split_ws_bytes), then the
+// tiled GEMM.
 hipError_t launch_mrconv(const void* x, const void* keys, const int32_t* idx, const void* W,
                          const void* bias, void* out, int B, int N, int M, int C, int Cout, int k,
                          int dt_bf16, int rt, void* split_ws, hipStream_t stream,

@@ -158,7 +158,8 @@ hipError_t launch_mrconv(const void* x, const void* keys, const int32_t* idx, co
 hipError_t launch_mrconv_gemm(const MrArgs& a, int dt_bf16, const void* split_ws,
                               hipStream_t stream, hipEvent_t ev0, hipEvent_t ev1) {
   GemmArgs ga;
-  ga.A = split_ws;
+  ga.A = dt_bf16 ? a.x : split_ws;  // bf16: x and m rows apart
+  ga.A2 = dt_bf16 ? split_ws : nullptr;
   ga.W = a.W;
   ga.bias = a.bias;
   ga.residual = nullptr;

@@ -120,7 +120,8 @@ __device__ __forceinline__ uint32_t bf16_pair_unsafe(uint32_t w) {
 // written.  Called by all 256 threads.
 // T3: three tasks per thread in flight instead of two (a caller with registers
 // to spare takes the 32-node tile's 768 tasks of C = 192 in one round).
-template <int DT, int KB, bool T3 = false, int LEAN = 0, bool COLS = false>
+// MONLY: only m_i is written (to dst + r * dst_stride).
+template <int DT, int KB, bool T3 = false, int LEAN = 0, bool COLS = false, bool MONLY = false>
 __device__ __forceinline__ void mr_gather_rows(const MrArgs& a, int row0, int TM,
                                                const int32_t* sIdx, char* dst, size_t dst_stride) {
   constexpr int ES = DT ? 2 : 4;
@@ -234,15 +235,17 @@ __device__ __forceinline__ void mr_gather_rows(const MrArgs& a, int row0, int TM
       for (int i = 0; i < VEC; ++i) mx[q][i] -= xf[i];
       if (row0 + r >= R) continue;
       char* d = dst + (size_t)r * dst_stride + cg * 16;
-      *reinterpret_cast<uint4*>(d) = xraw[q];
-      store_vec<DT>(d + C * ES, mx[q]);
+      if (!MONLY) *reinterpret_cast<uint4*>(d) = xraw[q];
+      store_vec<DT>(d + (MONLY ? 0 : C * ES), mx[q]);
     }
   }
 }
 
-// Gather-only tile of the two-pass MRConv: the [x_i | m_i] rows of TM nodes
-// from flattened node blk * TM, written to xcat [R, 2C].  sIdx: TM * k ints of
-// LDS.  Called by all 256 threads.
+// Gather-only tile of the two-pass MRConv: rows of TM nodes from flattened node
+// blk * TM, written to ws: [x_i | m_i] rows, [R, 2C]; in bf16, whose GEMM takes the
+// two halves of its contraction from two places, m_i rows alone, [R, C] (a third
+// of the gather's writes and reads of new lines; ViG-B gather 15.8 -> 12 us).
+// sIdx: TM * k ints of LDS.  Called by all 256 threads.
 constexpr int kMrGatherRows = 16;  // nodes per workgroup of the gather kernel
 
 template <int DT, int KB>
@@ -256,8 +259,9 @@ __device__ __forceinline__ void mr_gather_tile(const MrArgs& a, int blk, int TM,
     sIdx[e] = min(max(j, 0), a.M - 1) * (a.C * ES / 16);
   }
   __syncthreads();
-  const size_t stride = (size_t)2 * a.C * ES;
-  mr_gather_rows<DT, KB>(a, row0, TM, sIdx, static_cast<char*>(xcat) + row0 * stride, stride);
+  const size_t stride = (size_t)(DT ? 1 : 2) * a.C * ES;
+  mr_gather_rows<DT, KB, false, 0, false, DT == 1>(a, row0, TM, sIdx, static_cast<char*>(xcat) + row0 * stride,
+                                                   stride);
 }
 
 // TM = 16*RT nodes starting at flattened node row0.  smem holds
