@@ -211,7 +211,10 @@ hipError_t launch_cfg(const GemmArgs& a, hipStream_t stream, hipEvent_t ev0, hip
 //   128 x 64 (8)        23.8          16.4            9.8 *         8.5           7.5
 //   64 x 64 (4)         24.6          16.6           10.9           8.0 *         7.0
 //   32 x 64 (4)         32.6          21.1           11.6           8.9           5.4 *
-// (* the tile the rule takes: 490, 490, 588, 490 and 21 of them).  The tiles of
+// (* the tile the rule takes: 490, 490, 588, 490 and 21 of them).  Fewer than one
+// 64 x 64 tile per CU with 1 KB of K or more: 8 waves and 256 bytes of K per stage
+// (3136x1280x320 10.1 -> 8.5, 2208x976x264 8.5 -> 7.3; 3136x320x320 no gain;
+// 784x640x2560, two per CU, 9.4 -> 12.5).  The tiles of
 // 32 rows take 256 bytes of K per stage: on a grid of a few workgroups each
 // stage's round trip to memory shows.
 hipError_t launch_gemm_dma(const GemmArgs& a, hipStream_t stream, hipEvent_t ev0, hipEvent_t ev1) {
@@ -220,6 +223,8 @@ hipError_t launch_gemm_dma(const GemmArgs& a, hipStream_t stream, hipEvent_t ev0
   if (tiles(128, 128) >= 384 && 4 * pad128 <= 5 * pad64)
     return launch_cfg<DmaCfg<128, 128, 128, 4, 2>>(a, stream, ev0, ev1);
   if (tiles(128, 64) >= 384) return launch_cfg<DmaCfg<128, 64, 128, 4, 2>>(a, stream, ev0, ev1);
+  if (tiles(64, 64) >= 128 && tiles(64, 64) < 256 && a.K >= 512)
+    return launch_cfg<DmaCfg<64, 64, 256, 4, 2>>(a, stream, ev0, ev1);
   if (tiles(64, 64) >= 128) return launch_cfg<DmaCfg<64, 64, 128, 2, 2>>(a, stream, ev0, ev1);
   return launch_cfg<DmaCfg<32, 64, 256, 1, 4>>(a, stream, ev0, ev1);
 }

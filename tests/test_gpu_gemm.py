@@ -23,6 +23,8 @@ CASES = [
     ("64x64_ragged", 641, 136, 776, 1, True, True, 0),
     ("64x64_unaligned_out", 1300, 192, 448, 0, True, True, 1),
     ("64x64_aligned_8_bytes", 1300, 64, 456, 0, True, False, 4),
+    ("64x64_long_k", 1999, 520, 257, 0, True, True, 0),
+    ("64x64_long_k_gelu", 2208, 976, 264, 1, False, True, 0),
     ("32x64_ragged", 33, 264, 65, 0, True, True, 0),
     ("32x64_two_k_stages", 65, 128 + 8, 72, 1, False, True, 0),
     ("32x64_one_element", 1, 8, 1, 0, True, True, 0),
