@@ -146,8 +146,8 @@ gl_status gl_max_pool_nodes(const void* x, int B, int H, int W, int C, int r, gl
  * ever written.  Narrow layers gather straight into an on-chip tile and never
  * write the [B,N,2C] concatenation either.  When W is large per node (more
  * than 8 KB of W per node of the fused tile, e.g. C = Cout = 640) the call
- * runs two passes instead: the gather writes [x_i, m_i] rows to the caller's
- * workspace (B*N*2C*s bytes), then a tiled GEMM reads them.
+ * runs two passes instead: the gather writes [x_i, m_i] rows (bf16: m_i rows)
+ * to the caller's workspace (B*N*2C*s bytes), then a tiled GEMM reads them.
  * gl_mrconv_workspace_bytes() gives the size (0 when the fused tile is used;
  * workspace may then be NULL).  A NULL, short or not 16-byte aligned
  * workspace where one is needed returns GL_ERR_WORKSPACE; it must not overlap
@@ -243,7 +243,8 @@ gl_status gl_lookahead_destroy(gl_lookahead_t h);
 #define GL_TIME_BUILD 0
 #define GL_TIME_UPDATE 1
 #define GL_TIME_FUSED 2   /* one-launch blocks of GL_SCHED_LOOKAHEAD_FUSED */
-#define GL_TIME_LINEAR 3  /* fully connected layers of the full ViG block */
+#define GL_TIME_LINEAR 3  /* fully connected layers of the full ViG block (one record for
+                             FC2 and the FFN, and the next FC1, run in one launch) */
 gl_status gl_lookahead_set_profiling(gl_lookahead_t h, int max_records);
 gl_status gl_lookahead_kernel_times(gl_lookahead_t h, int which, float* ms_out, int cap,
                                     int* n_out);

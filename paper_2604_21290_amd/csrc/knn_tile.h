@@ -16,9 +16,9 @@
 //   3. the packed keys of the chunk go to an LDS strip [16][256];
 //   4. each query row is owned by 16 lanes of one wave; the row's running
 //      sorted list of the K' = k*dilation smallest keys lives in registers
-//      (element e = lane + 16*reg).  Chunk candidates below the list's K'-th
-//      key pass a threshold filter, are sorted per lane, and are merged 16 at
-//      a time: bitonic sort across the 16 lanes, then a bitonic merge into
+//      (element e = lane + 16*reg).  Each lane orders its few smallest chunk
+//      candidates, which are merged 16 at a time while any is below the list's
+//      K'-th key: bitonic sort across the 16 lanes, then a bitonic merge into
 //      the list that keeps its K' smallest.
 // The N x M distance matrix never leaves the chip; the only global write is
 // idx[B, N, k] (ranks 0, d, 2d, ... of the list).
