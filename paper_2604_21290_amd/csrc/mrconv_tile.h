@@ -210,10 +210,15 @@ __device__ __forceinline__ void mr_gather_rows(const MrArgs& a, int row0, int TM
       if (__any(unsafe != 0)) {  // rare: infinities, NaN, or magnitudes from 2^121 on
 #pragma unroll
         for (int q = 0; q < TPT; ++q) {
+          // the task's addresses again: kept until here they took the block kernel's
+          // 16-node tile past 168 VGPRs (three waves per SIMD), a spill; now 166
+          const int e = min(e0 + q * kMrThreads, ntask - 1), r = e / CG;
+          const int b = min(row0 + r, R - 1) / N;
+          const char* kb = static_cast<const char*>(a.keys) + ((size_t)b * M * C + (e - r * CG) * VEC) * ES;
 #pragma unroll 1
           for (int tt = 0; tt < k; ++tt) {
             float kf[VEC];
-            unpack_bf16x8(*reinterpret_cast<const uint4*>(kbase[q] + ((size_t)(uint32_t)nb[q][tt] << 4)), kf);
+            unpack_bf16x8(*reinterpret_cast<const uint4*>(kb + ((size_t)(uint32_t)sIdx[r * k + tt] << 4)), kf);
 #pragma unroll
             for (int i = 0; i < VEC; ++i) mx[q][i] = fmaxf(mx[q][i], kf[i]);
           }
