@@ -199,14 +199,25 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(KS > 4 
 
   // -- epilogue and selection, one row of each 16-lane group at a time -------
   const uint32_t qmax = a.qmax, mask = (1u << ib) - 1u;
+  // The scale pairs stay in registers; of 16 tiles the last eight are read for each
+  // row instead: with all of them the kernel spilled up to five VGPRs at its
+  // four waves per SIMD (16 x 4096 rows, 256 keys, us: C = 64 20.0 -> 18.8, 96 23.9 ->
+  // 22.7, 128 26.0 -> 24.7; K' = 64 45.5 -> 44.6, graphs identical).
+  constexpr int kHeld = KT == 16 ? 8 : KT;
   float2 sc[KT];
 #pragma unroll
-  for (int m = 0; m < KT; ++m) sc[m] = sScale[16 * m + t];
+  for (int m = 0; m < kHeld; ++m) sc[m] = sScale[16 * m + t];
   // (unrolled: a run-time v would select acc[m][v] and qr[v] out of four
   // registers on every tile)
 #pragma unroll
   for (int v = 0; v < 4; ++v) {
     uint32_t c16[16];
+    if constexpr (kHeld < KT) {
+      int at = 16 * kHeld + t;
+      asm volatile("" : "+v"(at));  // keeps the reads in this iteration
+#pragma unroll
+      for (int m = kHeld; m < KT; ++m) sc[m] = sScale[at + 16 * (m - kHeld)];
+    }
 #pragma unroll
     for (int m = 0; m < 16; ++m) {
       if (m < KT) {
