@@ -9,17 +9,23 @@ size_t knn_smem_bytes(int C, int dt_bf16) {
   return (size_t)kKnnRows * kKnnChunk * 4;
 }
 
-template <int DT, int R>
+template <int DT, int R, bool SKIP_NAN>
 __global__ __launch_bounds__(kKnnThreads) void knn_kernel(KnnArgs a) {
   extern __shared__ __align__(16) char smem[];
   const int nt = (a.N + kKnnRows - 1) / kKnnRows;
   const int blk = xcd_remap(blockIdx.x, gridDim.x);
   const int b = blk / nt, tile = blk - b * nt;
   constexpr int ES = DT ? 2 : 4;
-  knn_tile<DT, R>(smem, static_cast<const char*>(a.x) + (size_t)b * a.N * a.C * ES,
-                  static_cast<const char*>(a.keys) + (size_t)b * a.M * a.C * ES, a.N, a.C, a.M,
-                  a.k, a.dil, a.KK, a.ib, a.qscale, a.qmax, tile * kKnnRows,
-                  a.idx + (size_t)b * a.N * a.k);
+  knn_tile<DT, R, SKIP_NAN>(smem, static_cast<const char*>(a.x) + (size_t)b * a.N * a.C * ES,
+                            static_cast<const char*>(a.keys) + (size_t)b * a.M * a.C * ES, a.N, a.C,
+                            a.M, a.k, a.dil, a.KK, a.ib, a.qscale, a.qmax, tile * kKnnRows,
+                            a.idx + (size_t)b * a.N * a.k);
+}
+
+template <int DT, bool SKIP_NAN>
+const void* knn_fn(int R) {
+  return R == 1 ? (const void*)&knn_kernel<DT, 1, SKIP_NAN>
+         : R == 2 ? (const void*)&knn_kernel<DT, 2, SKIP_NAN> : (const void*)&knn_kernel<DT, 4, SKIP_NAN>;
 }
 
 KnnArgs make_knn_args(const void* x, const void* keys, int B, int N, int C, int M, int k, int dil,
@@ -49,14 +55,11 @@ hipError_t launch_knn_tile(const KnnArgs& a, int dt_bf16, hipStream_t stream, hi
   const size_t smem = knn_smem_bytes(a.C, dt_bf16);
   const dim3 grid(a.B * ((a.N + kKnnRows - 1) / kKnnRows)), block(kKnnThreads);
   const int R = knn_list_regs(a.KK);
-  const void* fn = nullptr;
-  if (dt_bf16) {
-    fn = R == 1 ? (const void*)&knn_kernel<1, 1> : R == 2 ? (const void*)&knn_kernel<1, 2>
-                                                          : (const void*)&knn_kernel<1, 4>;
-  } else {
-    fn = R == 1 ? (const void*)&knn_kernel<0, 1> : R == 2 ? (const void*)&knn_kernel<0, 2>
-                                                          : (const void*)&knn_kernel<0, 4>;
-  }
+  // Key sets that larger grids stream: non-finite rows rank as they do there,
+  // whatever the grid.
+  const bool skip = knn_use_stream(a.M, a.C, dt_bf16);
+  const void* fn = dt_bf16 ? (skip ? knn_fn<1, true>(R) : knn_fn<1, false>(R))
+                           : (skip ? knn_fn<0, true>(R) : knn_fn<0, false>(R));
   return launch_with_smem(fn, grid, block, smem, stream, ev0, ev1, a);
 }
 

@@ -173,7 +173,10 @@ __device__ __forceinline__ void select_chunk(uint32_t* L, uint32_t& tau, uint32_
 // One 16-row query tile of one image: rows row0 .. row0+15 of x_b against
 // all M keys of keys_b; writes idx_b[row, 0..k-1].  smem holds
 // knn_smem_bytes() bytes (the candidate strip).  Called by all 256 threads.
-template <int DT, int R>
+// A distance that is not a number (a NaN or an infinity in either row) ranks
+// first; SKIP_NAN: its key is left out, as the streamed kernel does, and places
+// of the list that no key takes stay all ones.
+template <int DT, int R, bool SKIP_NAN = false>
 __device__ __forceinline__ void knn_tile(char* smem, const char* __restrict__ xb,
                                          const char* __restrict__ kb, int N, int C, int M, int k,
                                          int dil, int KK, int ib, float qscale, uint32_t qmax,
@@ -290,7 +293,7 @@ __device__ __forceinline__ void knn_tile(char* smem, const char* __restrict__ xb
           const float d1s = fmaf(acc[p][v] * m2rjS, qr[v], baseS);
           const uint32_t q = min((uint32_t)fmaxf(d1s, 0.f), qmax);
           sStrip[(4 * g + v) * kKnnChunk + tt * 16 + t] =
-              (j < M) ? ((q << ib) | (uint32_t)j) : 0xffffffffu;
+              (j < M) && !(SKIP_NAN && d1s != d1s) ? ((q << ib) | (uint32_t)j) : 0xffffffffu;
         }
       }
     }

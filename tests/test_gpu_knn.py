@@ -304,3 +304,45 @@ def test_stream_and_tile_agree(case):
     rows = np.unique(np.linspace(0, N - 1, 24).astype(int))
     check_idx(all_[:1].cpu().numpy(), O.knn_distances(x.value[:1], rows=rows), k, d, rows=rows,
               label=label)
+
+
+# -- rows that are not finite, against more than 256 keys -----------------------------
+NON_FINITE = [
+    # label, B, N, C, k, d, dtype
+    ("k18", 26, 641, 40, 9, 2, I.BF16),
+    ("k9_eight_steps", 40, 450, 248, 9, 1, I.BF16),
+    ("k64_fp32", 33, 513, 36, 16, 4, I.F32),
+]
+
+
+@pytest.mark.parametrize("case", NON_FINITE, ids=[c[0] for c in NON_FINITE])
+def test_non_finite_rows_by_grid(case):
+    """A row with a NaN or an infinity has no distance to any other.  Against more
+    than 256 keys such keys are in no list, on a large grid (streamed) and on a
+    small one (in-register): a row's graph does not hang on its batch."""
+    require_gpu()
+    from paper_2604_21290_amd import api
+    label, B, N, C, k, d, dt = case
+    assert B * ((N + 15) // 16) > 1024 >= (N + 15) // 16 and N > 256
+    g = np.random.default_rng(N)
+    x = to_dev(I.random_features(N + C, B, N, C, dt, unit=False))
+    bad = torch.from_numpy(g.random((B, N)) < 0.1).cuda()
+    # the last image: too few finite rows to fill a list
+    bad[-1] = torch.arange(N, device="cuda") % 150 != 0
+    bad[-1, 1] = False
+    col = torch.from_numpy(g.integers(0, C, (B, N))).cuda()
+    val = torch.tensor([float("nan"), float("inf"), -float("inf")], device="cuda")
+    val = val[torch.from_numpy(g.integers(0, 3, (B, N))).cuda()].to(x.dtype)
+    at = torch.nonzero(bad, as_tuple=True)
+    x[at[0], at[1], col[at]] = val[at]
+    _say("non-finite", label)
+    all_ = api.knn_graph(x, k, d)
+    torch.cuda.synchronize()
+    good = ~bad[:-1]
+    for b in (0, B - 2):
+        idx = all_[b][good[b]].long()
+        assert int(idx.max()) < N and not bool(bad[b][idx].any()), (label, b)
+    for b in (0, B - 2, B - 1):
+        one = api.knn_graph(x[b:b + 1].contiguous(), k, d)
+        torch.cuda.synchronize()
+        assert torch.equal(one[0], all_[b]), (label, b)
