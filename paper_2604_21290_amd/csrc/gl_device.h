@@ -77,10 +77,17 @@ __device__ __forceinline__ uint32_t lds_offset(const void* p) {
   return (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) char*)p;
 }
 
-// `lds` is wave-uniform (it goes to M0); lanes that are off write nothing.
+// `lds` is wave-uniform (it goes to M0); lanes that are off write nothing.  M0 is
+// reserved, of which the compiler warns for each use, and named all the same: it
+// has values of its own there in kernels that move indexed registers or send
+// messages, and keeps none across a statement that lists it.
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Winline-asm"
 __device__ __forceinline__ void lds_dma16(const void* g, uint32_t lds) {
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(lds), "v"(g) : "memory");
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(lds), "v"(g)
+               : "memory", "m0");
 }
+#pragma clang diagnostic pop
 
 // This wave's direct loads have landed and its LDS reads are done; then the
 // workgroup's barrier.

@@ -49,3 +49,17 @@ def test_latency_bound_kernels_do_not_spill(tmp_path):
         assert ks, f"no {pat} instantiation found in {src}"
         bad = [(n, sc) for n, sc in ks if sc]
         assert not bad, f"{src}: kernels using scratch: {bad[:4]}"
+
+
+def test_asm_names_the_m0_it_writes():
+    """An asm statement that writes M0 lists it as clobbered: the compiler may hold
+    a value of its own there (indexed moves, messages, LDS loads it makes itself)."""
+    found = 0
+    for name in sorted(os.listdir(CSRC)):
+        with open(os.path.join(CSRC, name)) as f:
+            text = f.read()
+        for m in re.finditer(r"asm\s+volatile\s*\((.*?)\);", text, re.S):
+            if re.search(r"\bs_mov_b32 m0\b|\bm0, ", m.group(1)):
+                found += 1
+                assert '"m0"' in m.group(1).rsplit(":", 1)[-1], (name, m.group(0))
+    assert found
