@@ -9,8 +9,11 @@ size_t knn_smem_bytes(int C, int dt_bf16) {
   return (size_t)kKnnRows * kKnnChunk * 4;
 }
 
+// Three waves per SIMD.  bf16 gets them by itself (148 VGPRs and 16 accumulation
+// registers); fp32 took 156 to 162 and fell to two unless told (32 x 3136 rows, 196
+// keys, us, two waves / three: C = 48 66 / 52, C = 96 105 / 88).
 template <int DT, int R, bool SKIP_NAN>
-__global__ __launch_bounds__(kKnnThreads) void knn_kernel(KnnArgs a) {
+__global__ __launch_bounds__(kKnnThreads) __attribute__((amdgpu_waves_per_eu(DT ? 1 : 3, 8))) void knn_kernel(KnnArgs a) {
   extern __shared__ __align__(16) char smem[];
   const int nt = (a.N + kKnnRows - 1) / kKnnRows;
   const int blk = xcd_remap(blockIdx.x, gridDim.x);

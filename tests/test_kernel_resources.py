@@ -1,10 +1,12 @@
 """Register budget of the latency-bound kernels (CPU; compiles for gfx950).
 
 The one-launch block kernel, the fused MRConv and the in-register kNN run at
-three waves per SIMD, the lean MRConv and the resident-key kNN at four or more, the wide kNN at two; if the register allocator has to spill to scratch
-memory to meet that, they slow down without failing any parity test.  This
-test compiles their sources with the resource-usage remarks and requires no
-scratch for every instantiation of them."""
+three waves per SIMD, the lean MRConv and the resident-key kNN at four or more,
+the wide kNN at two; if the register allocator has to spill to scratch memory to
+meet that, or gives a wave up, they slow down without failing any parity test.
+This test compiles their sources with the resource-usage remarks and requires no
+scratch, and the waves where they hang on registers alone, for every
+instantiation of them."""
 import os
 import re
 import shutil
@@ -19,6 +21,7 @@ HIPCC = shutil.which("hipcc") or "/opt/rocm/bin/hipcc"
 KERNELS = {"block.hip": "block_kernel", "mrconv.hip": r"13mrconv_kernel|18mrconv_lean_kernel",
            "knn.hip": "knn_kernel", "knn_wide.hip": "knn_wide_kernel",
            "knn_resident.hip": "knn_resident_kernel"}
+WAVES = {"knn.hip": 3}  # its LDS holds three workgroups' waves and more
 
 
 def _usage(src: str, tmp) -> list:
@@ -29,14 +32,17 @@ def _usage(src: str, tmp) -> list:
            "-Rpass-analysis=kernel-resource-usage", os.path.join(CSRC, src), "-o", out]
     r = subprocess.run(cmd, capture_output=True, text=True, timeout=600)
     assert r.returncode == 0, r.stderr[-2000:]
-    rows, name = [], None
+    rows, name, scratch = [], None, 0
     for line in r.stderr.splitlines():
         m = re.search(r"Function Name: (\S+)", line)
         if m:
             name = m.group(1)
         m = re.search(r"ScratchSize \[bytes/lane\]: (\d+)", line)
+        if m:
+            scratch = int(m.group(1))
+        m = re.search(r"Occupancy \[waves/SIMD\]: (\d+)", line)
         if m and name:
-            rows.append((name, int(m.group(1))))
+            rows.append((name, scratch, int(m.group(1))))
     return rows
 
 
@@ -45,10 +51,12 @@ def test_latency_bound_kernels_do_not_spill(tmp_path):
     with ThreadPoolExecutor(len(KERNELS)) as ex:
         res = dict(zip(KERNELS, ex.map(lambda s: _usage(s, tmp_path), KERNELS)))
     for src, pat in KERNELS.items():
-        ks = [(n, sc) for n, sc in res[src] if re.search(pat, n)]
+        ks = [r for r in res[src] if re.search(pat, r[0])]
         assert ks, f"no {pat} instantiation found in {src}"
-        bad = [(n, sc) for n, sc in ks if sc]
+        bad = [(n, sc) for n, sc, _ in ks if sc]
         assert not bad, f"{src}: kernels using scratch: {bad[:4]}"
+        bad = [(n, occ) for n, _, occ in ks if occ < WAVES.get(src, 1)]
+        assert not bad, f"{src}: kernels short of waves: {bad[:4]}"
 
 
 def test_asm_names_the_m0_it_writes():
