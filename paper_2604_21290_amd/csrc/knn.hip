@@ -66,18 +66,41 @@ hipError_t launch_knn_tile(const KnnArgs& a, int dt_bf16, hipStream_t stream, hi
   return launch_with_smem(fn, grid, block, smem, stream, ev0, ev1, a);
 }
 
+// Tiles of 16 query rows up to which more than 256 keys are ranked by the
+// in-register kernel, which packs the same keys, instead of the streamed one.
+// A streamed workgroup lives for one wave's sweep of all keys, whatever the grid;
+// here four waves share the sweep of 16 rows, so time grows with the workgroups, in
+// steps of one per CU, and with the key rows that each reads from L2.  Rows of
+// whole 128-byte lines cost it most: a k-step's 64 bytes of a row are half a line,
+// and at those strides the 64 rows in flight displace the other halves in L1.
+// us, streamed / in-register, k = 9, d = 2:
+//   bf16, M = 1024      512 tiles    768        1024      M = 4096, 1024 tiles
+//   C = 96               55 / 19    55 / 24    56 / 32    140 / 108
+//   C = 192              65 / 35    65 / 47    65 / 64    187 / 239
+//   C = 256              76 / 47    76 / 65    76 / 88    243 / 340
+//   C = 640             127 / 101  126 / 146  126 / 192   468 / 754
+// and, streamed over in-register at 1024 tiles, M = 300 and 4096: bf16 C = 160 1.5,
+// 1.2, 248 1.3, 1.1, 368 1.2, 1.3, 480 1.1, 1.3; 64 1.6, 0.97 (768: 2.1, 1.3); 304 1.1,
+// 1.0 and 600 0.9, 0.9 (768: 1.3, 1.3 and 1.1, 1.2); fp32 C = 96 1.5, 1.3,
+// 128 1.3, 1.2, 252 1.1, 1.2, 360 1.3, 1.4; 64 1.4, 1.02 and 160 0.9, 0.8 (768: 1.8, 1.4 and
+// 1.1, 1.1).  From 12 contraction steps on streamed workgroups of 64 rows run one
+// per CU: where they need a second round, in-register is 1.3 to 2.1 times as fast.
+static bool knn_few_tiles(int B, int N, int C, int dt_bf16) {
+  const long long tiles = (long long)B * ((N + kKnnRows - 1) / kKnnRows);
+  if (tiles > 1024) return false;
+  const int rowb = C * (dt_bf16 ? 2 : 4), steps = (rowb + 63) / 64;
+  if (steps > 8 && (long long)B * ((N + 63) / 64) > 256) return true;
+  int limit = 1024;
+  if (rowb % 128 == 0) limit = dt_bf16 ? (rowb > 128 ? 512 : 768) : rowb == 256 || rowb > 512 ? 768 : 1024;
+  else if (dt_bf16 && (steps == 10 || (steps > 16 && steps <= 20))) limit = 768;
+  return tiles <= limit;
+}
+
 hipError_t launch_knn(const void* x, const void* keys, int B, int N, int C, int M, int k,
                       int dil, int dt_bf16, int32_t* idx_out, hipStream_t stream,
                       hipEvent_t ev0, hipEvent_t ev1) {
   const KnnArgs a = make_knn_args(x, keys, B, N, C, M, k, dil, idx_out);
-  // Large key sets on small grids take the in-register kernel, which ranks the
-  // same packed keys.  A streamed workgroup lives for one wave's sweep of all
-  // keys, whatever the grid; here four waves share the sweep of 16 rows, so
-  // time grows with the workgroups instead.  us, streamed / in-register, k = 9,
-  // d = 2: 3 x 513, C = 204, fp32 89 / 27 (99 workgroups); bf16 1 x 3136, C = 96
-  // 106 / 41 (196), 12 x 1024, C = 200 69 / 48 (768), 32 x 513, C = 200 47.8 / 46.2
-  // (1056), 12 x 2048, C = 200 126 / 176 (1536), 32 x 1024, C = 96 54 / 59 (2048).
-  if (knn_use_stream(M, C, dt_bf16) && (long long)B * ((N + kKnnRows - 1) / kKnnRows) <= 1024)
+  if (knn_use_stream(M, C, dt_bf16) && knn_few_tiles(B, N, C, dt_bf16))
     return launch_knn_tile(a, dt_bf16, stream, ev0, ev1);
   if (knn_use_stream(M, C, dt_bf16)) return launch_knn_stream(a, dt_bf16, stream, ev0, ev1);
   if (knn_use_resident(B, N, M, C, dt_bf16)) return launch_knn_resident(a, stream, ev0, ev1);

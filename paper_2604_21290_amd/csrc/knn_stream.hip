@@ -530,7 +530,7 @@ int knn_stream_ks(int C, int dt_bf16) {
   return 0;
 }
 
-// Large key sets, on grids past 1024 tiles of 16 rows (launch_knn).  (For many
+// Large key sets, on grids that are not small (knn_few_tiles, knn.hip).  (For many
 // query rows against a small key set, e.g. 3136 rows x 196 pooled keys, the
 // in-register kernel measured faster.)
 bool knn_use_stream(int M, int C, int dt_bf16) {

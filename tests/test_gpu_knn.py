@@ -306,6 +306,35 @@ def test_stream_and_tile_agree(case):
               label=label)
 
 
+# -- ... and the widths whose limit lies below 1024 tiles ------------------------------
+GRID_RULE = [
+    # B images of N nodes, 513..1024 tiles of 16 rows: rows of whole 128-byte lines
+    # past 512 or 768 tiles and one image less, other widths, two rounds of streamed
+    # workgroups
+    (9, 1000, 128, I.BF16), (8, 1024, 128, I.BF16), (13, 1000, 64, I.BF16), (12, 1024, 64, I.BF16),
+    (16, 1024, 72, I.BF16), (9, 1024, 320, I.BF16), (13, 1024, 304, I.BF16), (13, 1024, 600, I.BF16),
+    (20, 784, 384, I.BF16), (13, 1024, 160, I.F32), (12, 1024, 160, I.F32), (16, 1024, 128, I.F32),
+]
+
+
+@pytest.mark.parametrize("B,N,C,dt", GRID_RULE)
+def test_grid_rule_edges(B, N, C, dt):
+    """A batch on either side of its width's limit and its first and last image
+    alone give the same graph, which is the oracle's."""
+    require_gpu()
+    from paper_2604_21290_amd import api
+    x = I.random_features(N + C, B, N, C, dt, unit=False)
+    xd = to_dev(x)
+    _say("grid rule", B, N, C, dt)
+    all_ = api.knn_graph(xd, 9, 2)
+    for b in (0, B - 1):
+        one = api.knn_graph(xd[b:b + 1].contiguous(), 9, 2)
+        torch.cuda.synchronize()
+        assert torch.equal(one[0], all_[b]), b
+    rows = np.unique(np.linspace(0, N - 1, 24).astype(int))
+    check_idx(all_[:1].cpu().numpy(), O.knn_distances(x.value[:1], rows=rows), 9, 2, rows=rows)
+
+
 # -- rows that are not finite, against more than 256 keys -----------------------------
 NON_FINITE = [
     # label, B, N, C, k, d, dtype
