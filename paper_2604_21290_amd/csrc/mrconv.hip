@@ -34,8 +34,8 @@ __global__ __launch_bounds__(kMrThreads) __attribute__((amdgpu_waves_per_eu(3, 8
   mrconv_tile<DT, RT, KB, false, false, false, 0, ACT>(smem, a, blk * 16 * RT);
 }
 
-// Narrow layers over many node tiles: NC output tiles per wave, the layer in one
-// pass, and one gather task per thread.
+// Narrow layers over many node tiles: NC output tiles per wave and pass (bf16: the
+// layer in one pass), and one gather task per thread.
 template <int DT, int RT, int KB, int NC, bool ACT = false>
 __global__ __launch_bounds__(kMrThreads) __attribute__((amdgpu_waves_per_eu(RT * NC == 12 && ACT ? 3 : 4, 8))) void mrconv_lean_kernel(MrArgs a) {
   extern __shared__ __align__(16) char smem[];
@@ -213,17 +213,17 @@ hipError_t launch_mrconv_args(const MrArgs& a0, int dt_bf16, int rt, void* split
     fn = dt_bf16 ? (rt == 2 ? mrconv_fn_kb<1, 2, true>(KB) : mrconv_fn_kb<1, 1, true>(KB))
                  : (rt == 2 ? mrconv_fn_kb<0, 2, true>(KB) : mrconv_fn_kb<0, 1, true>(KB));
   } else if (mrconv_use_lean(a.C, Cout, row_tiles)) {
-    // 64-node tiles when they fit 64 KB of LDS (measured 2-3 % faster than 32),
-    // up to 192 columns (three output tiles per wave)
+    // 64-node tiles when they fit 64 KB of LDS (measured 2-3 % faster than 32); in
+    // bf16 up to 192 columns (three output tiles per wave)
     const int nc = nct <= 8 ? 2 : nct <= 12 ? 3 : 4;
-    if (nc < 4 && mrconv_smem_bytes(C, k, dt_bf16, 4) <= 65536) {
-      fn = dt_bf16 ? (nc == 2 ? mrconv_fn_act<1, 4, false, 2>(KB, act) : mrconv_fn_act<1, 4, false, 3>(KB, act))
-                   : (nc == 2 ? mrconv_fn_act<0, 4, false, 2>(KB, act) : mrconv_fn_act<0, 4, false, 3>(KB, act));
+    if ((!dt_bf16 || nc < 4) && mrconv_smem_bytes(C, k, dt_bf16, 4) <= 65536) {
+      fn = !dt_bf16 ? mrconv_fn_act<0, 4, false, 1>(KB, act)
+           : nc == 2 ? mrconv_fn_act<1, 4, false, 2>(KB, act) : mrconv_fn_act<1, 4, false, 3>(KB, act);
       return launch_with_smem(fn, dim3((a.R + 63) / 64), block, mrconv_smem_bytes(C, k, dt_bf16, 4),
                               stream, ev0, ev1, a);
     }
     fn = dt_bf16 ? (rt == 2 ? mrconv_fn_act<1, 2, false, 4>(KB, act) : mrconv_fn_act<1, 1, false, 4>(KB, act))
-                 : (rt == 2 ? mrconv_fn_act<0, 2, false, 4>(KB, act) : mrconv_fn_act<0, 1, false, 4>(KB, act));
+                 : (rt == 2 ? mrconv_fn_act<0, 2, false, 1>(KB, act) : mrconv_fn_act<0, 1, false, 1>(KB, act));
   } else {
     fn = dt_bf16 ? (rt == 2 ? mrconv_fn_act<1, 2>(KB, act) : mrconv_fn_act<1, 1>(KB, act))
                  : (rt == 2 ? mrconv_fn_act<0, 2>(KB, act) : mrconv_fn_act<0, 1>(KB, act));

@@ -62,9 +62,11 @@ __device__ __forceinline__ bool mr_step_needed(const MrArgs& a, int n0, int s, i
 // COLS: only output tiles tile0 .. tile_end-1 (a column group of a small grid),
 // one tile per wave and pass, with the W operands of kMrKUCols k-steps per batch.
 constexpr int kMrKUCols = 12;
-// LEAN > 0: that many output tiles per wave, which take the layer in one pass, and
-// one gather task per thread and round, for layers of few output tiles that run
-// many node tiles: the registers saved buy more waves per SIMD.
+// LEAN > 0: one gather task per thread and round, and that many output tiles per
+// wave and pass, for layers of few output tiles that run many node tiles: the
+// registers saved buy more waves per SIMD.  bf16 takes the layer in one pass (LEAN >
+// 1), fp32, whose steps are four MFMAs, a tile at a time (25088 nodes, k = 9, us, one
+// pass / a tile: C = 48 14.9 / 11.1, C = 160 62.7 / 53.5, C = 252, Cout = 88, k = 4 84 / 62).
 template <bool COLS, int LEAN = 0> struct MrBatch {
   static constexpr int KU = COLS ? kMrKUCols : LEAN > 2 ? 2 : kMrKU;  // k-steps per batch of W operands
   static constexpr int NC = COLS ? 1 : LEAN ? LEAN : 4;    // output tiles per wave and pass
@@ -137,9 +139,10 @@ __device__ __forceinline__ void mr_gather_rows(const MrArgs& a, int row0, int TM
   // slower: 3 x 513, C = 204, k = 12, fp32 15.8 -> 25.1 us)
   constexpr int TPT = COLS ? (KB <= 9 ? 3 : 1) : KB <= 9 && !LEAN ? (T3 ? 3 : 2) : 1;
   const int ntask = TM * CG;
-  // Task e is vector e % CG of node e / CG; a thread's tasks are kMrThreads apart,
-  // so (node, vector) advance by a fixed step and one carry.  The tile's nodes
-  // lie in image b0 or, when an image has at least TM nodes, the next one.
+  // Task e is vector e % CG of node e / CG; in bf16 a thread's tasks, kMrThreads
+  // apart, advance (node, vector) by a fixed step and one carry, and the tile's nodes
+  // lie in image b0 or, when an image has at least TM nodes, the next one.  fp32
+  // divides (196 nodes, C = 252, Cout = 88, k = 12: 11.8 us with the steps, 11.3 without).
   const int b0 = row0 / N, row1 = (b0 + 1) * N;
   const bool one_edge = N >= TM;
   const int dr = kMrThreads / CG, dc = kMrThreads - dr * CG;
@@ -154,17 +157,25 @@ __device__ __forceinline__ void mr_gather_rows(const MrArgs& a, int row0, int TM
 #pragma unroll
     for (int q = 0; q < TPT; ++q) {
       // past the last task: the last node's rows again (not written)
-      const int r = min(tr, TM - 1), cg = tc;
-      nr[q] = tr;
-      nc[q] = tc;
-      tr += dr;
-      tc += dc;
-      if (tc >= CG) {
-        tc -= CG;
-        ++tr;
+      int r, cg;
+      if constexpr (DT) {
+        r = min(tr, TM - 1);
+        cg = tc;
+        nr[q] = tr;
+        nc[q] = tc;
+        tr += dr;
+        tc += dc;
+        if (tc >= CG) {
+          tc -= CG;
+          ++tr;
+        }
+      } else {
+        const int e = min(e0 + q * kMrThreads, ntask - 1);
+        nr[q] = r = e / CG;
+        nc[q] = cg = e - r * CG;
       }
       const int row = min(row0 + r, R - 1);
-      const int b = one_edge ? b0 + (row >= row1) : row / N;
+      const int b = DT && one_edge ? b0 + (row >= row1) : row / N;
       xraw[q] = *reinterpret_cast<const uint4*>(static_cast<const char*>(a.x) +
                                                 ((size_t)row * C + cg * VEC) * ES);
       kbase[q] = static_cast<const char*>(a.keys) + ((size_t)b * M * C + cg * VEC) * ES;
@@ -321,9 +332,11 @@ __device__ __forceinline__ void mrconv_tile(char* smem, const MrArgs& a, int row
   // operands of the next batch of k-steps are requested before the current
   // batch is multiplied, so no batch after the first waits on its own loads.
   constexpr bool PIPE = T3 && !HEADS && !COLS && !LEAN;
+  // one pass, which every wave takes: its epilogue has barriers
+  constexpr bool ONE = LEAN > 1;
+  static_assert(!ONE || DT, "the one-pass epilogue is written for bf16");
   uint4 bw2[KU][NC] = {};
-  // (the lean tile is one pass, which every wave takes: its epilogue has barriers)
-  for (int p = 0; LEAN > 0 ? p == 0 : T0 + w + 4 * NC * p < TE; ++p) {
+  for (int p = 0; ONE ? p == 0 : T0 + w + 4 * NC * p < TE; ++p) {
     f32x4 acc[RT][NC];
 #pragma unroll
     for (int rt = 0; rt < RT; ++rt)
@@ -353,14 +366,14 @@ __device__ __forceinline__ void mrconv_tile(char* smem, const MrArgs& a, int row
 #pragma unroll
           for (int rt = 0; rt < RT; ++rt) {
             if (DT) {
-              acc[rt][c4] = LEAN ? mfma_bf16(bv, af[rt], acc[rt][c4]) : mfma_bf16(af[rt], bv, acc[rt][c4]);
+              acc[rt][c4] = ONE ? mfma_bf16(bv, af[rt], acc[rt][c4]) : mfma_bf16(af[rt], bv, acc[rt][c4]);
             } else {
               const float4 x4 = __builtin_bit_cast(float4, af[rt]);
               const float4 w4 = __builtin_bit_cast(float4, bv);
-              acc[rt][c4] = LEAN ? mfma_f32(w4.x, x4.x, acc[rt][c4]) : mfma_f32(x4.x, w4.x, acc[rt][c4]);
-              acc[rt][c4] = LEAN ? mfma_f32(w4.y, x4.y, acc[rt][c4]) : mfma_f32(x4.y, w4.y, acc[rt][c4]);
-              acc[rt][c4] = LEAN ? mfma_f32(w4.z, x4.z, acc[rt][c4]) : mfma_f32(x4.z, w4.z, acc[rt][c4]);
-              acc[rt][c4] = LEAN ? mfma_f32(w4.w, x4.w, acc[rt][c4]) : mfma_f32(x4.w, w4.w, acc[rt][c4]);
+              acc[rt][c4] = mfma_f32(x4.x, w4.x, acc[rt][c4]);
+              acc[rt][c4] = mfma_f32(x4.y, w4.y, acc[rt][c4]);
+              acc[rt][c4] = mfma_f32(x4.z, w4.z, acc[rt][c4]);
+              acc[rt][c4] = mfma_f32(x4.w, w4.w, acc[rt][c4]);
             }
           }
         }
@@ -387,14 +400,15 @@ __device__ __forceinline__ void mrconv_tile(char* smem, const MrArgs& a, int row
       }
     }
     // -- epilogue: + bias, [GELU], round once, store --------------------------------
-    if constexpr (LEAN > 0) {
-    // The lean tile's operands were swapped (W first), so lane (g, t) holds
+    if constexpr (ONE) {
+    // The operands were swapped (W first), so lane (g, t) holds
     // columns n .. n+3 of node 16 rt + t.  The layer is one pass: its rows go
     // into the A-tile, when they fit there, and are stored whole, 16 bytes a lane
     // (C = 160, 25088 nodes: 17.5 -> 15.8 us against 2-byte stores; the two
     // barriers cost the other tiles more than that gains); else four columns a
     // lane, or one where a row is not a multiple of four.
-    const bool rows = Cout <= 2 * C && (Cout * ES & 15) == 0;  // uniform
+    const bool rows = Cout <= 2 * C && (Cout & 7) == 0;  // uniform
+    uint16_t* out = static_cast<uint16_t*>(a.out);
     if (rows) __syncthreads();  // every wave is done with the A-tile
 #pragma unroll
     for (int c4 = 0; c4 < NC; ++c4) {
@@ -402,14 +416,8 @@ __device__ __forceinline__ void mrconv_tile(char* smem, const MrArgs& a, int row
       const int n = (T0 + w + 4 * (NC * p + c4)) * 16 + 4 * g;
       float bn[4];
 #pragma unroll
-      for (int v = 0; v < 4; ++v) {
-        bn[v] = 0.f;
-        if (a.bias) {
-          const int nc = min(n + v, Cout - 1);
-          bn[v] = DT ? bf16_bits_to_f32(static_cast<const uint16_t*>(a.bias)[nc])
-                     : static_cast<const float*>(a.bias)[nc];
-        }
-      }
+      for (int v = 0; v < 4; ++v)
+        bn[v] = a.bias ? bf16_bits_to_f32(static_cast<const uint16_t*>(a.bias)[min(n + v, Cout - 1)]) : 0.f;
 #pragma unroll
       for (int rt = 0; rt < RT; ++rt) {
         float y[4];
@@ -421,25 +429,15 @@ __device__ __forceinline__ void mrconv_tile(char* smem, const MrArgs& a, int row
         const uint2 y2 = make_uint2(f32x2_to_bf16x2_bits(y[0], y[1]), f32x2_to_bf16x2_bits(y[2], y[3]));
         const int r = rt * 16 + t, row = row0 + r;
         if (rows) {
-          char* d = sA + r * lds_row + n * ES;
-          if (n < Cout) {
-            if (DT) *reinterpret_cast<uint2*>(d) = y2;
-            else *reinterpret_cast<float4*>(d) = make_float4(y[0], y[1], y[2], y[3]);
-          }
+          if (n < Cout) *reinterpret_cast<uint2*>(sA + r * lds_row + n * 2) = y2;
         } else if (row < R) {
-          const size_t o = (size_t)row * Cout + n;
+          uint16_t* d = out + (size_t)row * Cout + n;
           if ((Cout & 3) == 0) {
-            if (n < Cout) {
-              if (DT) *reinterpret_cast<uint2*>(static_cast<uint16_t*>(a.out) + o) = y2;
-              else *reinterpret_cast<float4*>(static_cast<float*>(a.out) + o) = make_float4(y[0], y[1], y[2], y[3]);
-            }
+            if (n < Cout) *reinterpret_cast<uint2*>(d) = y2;
           } else {
 #pragma unroll
             for (int v = 0; v < 4; ++v)
-              if (n + v < Cout) {
-                if (DT) static_cast<uint16_t*>(a.out)[o + v] = (uint16_t)f32_to_bf16_bits(y[v]);
-                else static_cast<float*>(a.out)[o + v] = y[v];
-              }
+              if (n + v < Cout) d[v] = (uint16_t)f32_to_bf16_bits(y[v]);
           }
         }
       }
@@ -447,12 +445,12 @@ __device__ __forceinline__ void mrconv_tile(char* smem, const MrArgs& a, int row
     if (rows) {
       __syncthreads();
       // the tile's rows are contiguous in out
-      const int vr = Cout * ES / 16, nv = min(TM, R - row0) * vr;
-      char* d = static_cast<char*>(a.out) + (size_t)row0 * Cout * ES;
+      const int vr = Cout / 8, nv = min(TM, R - row0) * vr;
+      uint16_t* d = out + (size_t)row0 * Cout;
       const int er = kMrThreads / vr, ec = kMrThreads - er * vr;
       int r = tid / vr, c = tid - r * vr;
       for (int e = tid; e < nv; e += kMrThreads) {
-        *reinterpret_cast<uint4*>(d + (size_t)e * 16) = *reinterpret_cast<const uint4*>(sA + r * lds_row + c * 16);
+        *reinterpret_cast<uint4*>(d + (size_t)e * 8) = *reinterpret_cast<const uint4*>(sA + r * lds_row + c * 16);
         r += er;
         c += ec;
         if (c >= vr) {

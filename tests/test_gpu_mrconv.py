@@ -215,6 +215,9 @@ PACKED = [
     ("lean_three_tiles", 33, 260, 168, 16, 168, I.BF16),
     ("lean_four_tiles", 33, 260, 136, 9, 200, I.BF16),
     ("lean_fp32", 33, 260, 68, 9, 68, I.F32),
+    ("lean_fp32_cout_33", 33, 260, 40, 12, 33, I.F32),
+    ("lean_fp32_four_passes", 33, 260, 68, 4, 250, I.F32),
+    ("lean_fp32_32_nodes", 33, 260, 252, 4, 88, I.F32),
     ("two_pass", 2, 150, 640, 9, 648, I.BF16),
     ("fp32", 3, 77, 36, 9, 40, I.F32),
 ]
