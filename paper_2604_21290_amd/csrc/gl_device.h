@@ -95,6 +95,17 @@ __device__ __forceinline__ void dma_wait_barrier() {
   asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
 }
 
+// 16 or 8 bytes at any place of a bf16 tensor (one global access: the hardware
+// splits those that cross a line)
+typedef uint32_t u32x2_any __attribute__((ext_vector_type(2), aligned(2), may_alias));
+typedef uint32_t u32x4_any __attribute__((ext_vector_type(4), aligned(2), may_alias));
+__device__ __forceinline__ void store16_any(void* p, uint4 v) {
+  *static_cast<u32x4_any*>(p) = __builtin_bit_cast(u32x4_any, v);
+}
+__device__ __forceinline__ void store8_any(void* p, uint2 v) {
+  *static_cast<u32x2_any*>(p) = __builtin_bit_cast(u32x2_any, v);
+}
+
 // ---------------------------------------------------------------------------
 // cross-lane moves inside each row of 16 lanes, as DPP modifiers (no LDS trip)
 // ---------------------------------------------------------------------------

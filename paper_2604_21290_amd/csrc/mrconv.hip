@@ -34,7 +34,7 @@ __global__ __launch_bounds__(kMrThreads) __attribute__((amdgpu_waves_per_eu(3, 8
   mrconv_tile<DT, RT, KB, false, false, false, 0, ACT>(smem, a, blk * 16 * RT);
 }
 
-// Narrow layers over many node tiles: NC output tiles per wave and pass (bf16: the
+// Narrow layers over many node tiles: NC output tiles per wave and pass (NC > 1: the
 // layer in one pass), and one gather task per thread.
 template <int DT, int RT, int KB, int NC, bool ACT = false>
 __global__ __launch_bounds__(kMrThreads) __attribute__((amdgpu_waves_per_eu(RT * NC == 12 && ACT ? 3 : 4, 8))) void mrconv_lean_kernel(MrArgs a) {
@@ -213,17 +213,28 @@ hipError_t launch_mrconv_args(const MrArgs& a0, int dt_bf16, int rt, void* split
     fn = dt_bf16 ? (rt == 2 ? mrconv_fn_kb<1, 2, true>(KB) : mrconv_fn_kb<1, 1, true>(KB))
                  : (rt == 2 ? mrconv_fn_kb<0, 2, true>(KB) : mrconv_fn_kb<0, 1, true>(KB));
   } else if (mrconv_use_lean(a.C, Cout, row_tiles)) {
-    // 64-node tiles when they fit 64 KB of LDS (measured 2-3 % faster than 32); in
-    // bf16 up to 192 columns (three output tiles per wave)
-    const int nc = nct <= 8 ? 2 : nct <= 12 ? 3 : 4;
-    if ((!dt_bf16 || nc < 4) && mrconv_smem_bytes(C, k, dt_bf16, 4) <= 65536) {
-      fn = !dt_bf16 ? mrconv_fn_act<0, 4, false, 1>(KB, act)
-           : nc == 2 ? mrconv_fn_act<1, 4, false, 2>(KB, act) : mrconv_fn_act<1, 4, false, 3>(KB, act);
-      return launch_with_smem(fn, dim3((a.R + 63) / 64), block, mrconv_smem_bytes(C, k, dt_bf16, 4),
-                              stream, ev0, ev1, a);
+    // 64-node tiles when they fit 64 KB of LDS (measured 2-3 % faster than 32), in
+    // bf16 in one pass of two or three output tiles per wave.  A tile at a time is
+    // faster where a wave has one tile, and past 192 columns, where four tiles' sums
+    // leave room for 32 nodes (us, k = 9, one pass / a tile: 25088 nodes, C = 48 6.6 /
+    // 6.2, C = 96, Cout = 37 9.3 / 8.0, C = 64, Cout = 256 17.0 / 12.4, 128, 256 23.3 / 17.0,
+    // 96, 200 17.6 / 15.8).  Two tiles a wave on less than one 64-node tile per CU
+    // take 32 nodes (12544 nodes, C = 80: 8.2 -> 7.2; three tiles lose, C = 192 14.2 -> 15.3).
+    const int nc = !dt_bf16 || nct <= 4 || nct > 12 ? 1 : nct <= 8 ? 2 : 3;
+    if (mrconv_smem_bytes(C, k, dt_bf16, 4) <= 65536) {
+      if (nc == 2 && rt == 2 && (a.R + 63) / 64 < 256) {
+        fn = mrconv_fn_act<1, 2, false, 2>(KB, act);
+      } else {
+        fn = !dt_bf16 ? mrconv_fn_act<0, 4, false, 1>(KB, act)
+             : nc == 1 ? mrconv_fn_act<1, 4, false, 1>(KB, act)
+             : nc == 2 ? mrconv_fn_act<1, 4, false, 2>(KB, act) : mrconv_fn_act<1, 4, false, 3>(KB, act);
+        return launch_with_smem(fn, dim3((a.R + 63) / 64), block, mrconv_smem_bytes(C, k, dt_bf16, 4),
+                                stream, ev0, ev1, a);
+      }
+    } else {
+      fn = dt_bf16 ? (rt == 2 ? mrconv_fn_act<1, 2, false, 4>(KB, act) : mrconv_fn_act<1, 1, false, 4>(KB, act))
+                   : (rt == 2 ? mrconv_fn_act<0, 2, false, 1>(KB, act) : mrconv_fn_act<0, 1, false, 1>(KB, act));
     }
-    fn = dt_bf16 ? (rt == 2 ? mrconv_fn_act<1, 2, false, 4>(KB, act) : mrconv_fn_act<1, 1, false, 4>(KB, act))
-                 : (rt == 2 ? mrconv_fn_act<0, 2, false, 1>(KB, act) : mrconv_fn_act<0, 1, false, 1>(KB, act));
   } else {
     fn = dt_bf16 ? (rt == 2 ? mrconv_fn_act<1, 2>(KB, act) : mrconv_fn_act<1, 1>(KB, act))
                  : (rt == 2 ? mrconv_fn_act<0, 2>(KB, act) : mrconv_fn_act<0, 1>(KB, act));

@@ -64,7 +64,7 @@ __device__ __forceinline__ bool mr_step_needed(const MrArgs& a, int n0, int s, i
 constexpr int kMrKUCols = 12;
 // LEAN > 0: one gather task per thread and round, and that many output tiles per
 // wave and pass, for layers of few output tiles that run many node tiles: the
-// registers saved buy more waves per SIMD.  bf16 takes the layer in one pass (LEAN >
+// registers saved buy more waves per SIMD.  bf16 takes most layers in one pass (LEAN >
 // 1), fp32, whose steps are four MFMAs, a tile at a time (25088 nodes, k = 9, us, one
 // pass / a tile: C = 48 14.9 / 11.1, C = 160 62.7 / 53.5, C = 252, Cout = 88, k = 4 84 / 62).
 template <bool COLS, int LEAN = 0> struct MrBatch {
@@ -401,13 +401,13 @@ __device__ __forceinline__ void mrconv_tile(char* smem, const MrArgs& a, int row
     }
     // -- epilogue: + bias, [GELU], round once, store --------------------------------
     if constexpr (ONE) {
-    // The operands were swapped (W first), so lane (g, t) holds
-    // columns n .. n+3 of node 16 rt + t.  The layer is one pass: its rows go
-    // into the A-tile, when they fit there, and are stored whole, 16 bytes a lane
-    // (C = 160, 25088 nodes: 17.5 -> 15.8 us against 2-byte stores; the two
-    // barriers cost the other tiles more than that gains); else four columns a
-    // lane, or one where a row is not a multiple of four.
-    const bool rows = Cout <= 2 * C && (Cout & 7) == 0;  // uniform
+    // The operands were swapped (W first), so lane (g, t) holds columns n .. n+3 of
+    // node 16 rt + t.  The layer is one pass: its rows go into the A-tile, when they
+    // fit there, and are stored whole, 16 bytes a lane whatever their alignment (C =
+    // 160, 25088 nodes, us, against 2-byte stores: 160 columns 17.6 -> 15.6, 157 18.3 ->
+    // 16.9; the two barriers cost the other tiles more than that gains); else four
+    // columns a lane.  A row's last columns, short of a store, go one by one.
+    const bool rows = Cout <= 2 * C;  // uniform
     uint16_t* out = static_cast<uint16_t*>(a.out);
     if (rows) __syncthreads();  // every wave is done with the A-tile
 #pragma unroll
@@ -428,15 +428,15 @@ __device__ __forceinline__ void mrconv_tile(char* smem, const MrArgs& a, int row
         }
         const uint2 y2 = make_uint2(f32x2_to_bf16x2_bits(y[0], y[1]), f32x2_to_bf16x2_bits(y[2], y[3]));
         const int r = rt * 16 + t, row = row0 + r;
-        if (rows) {
+        if (rows) {  // (up to three columns past Cout fall into the row's padding)
           if (n < Cout) *reinterpret_cast<uint2*>(sA + r * lds_row + n * 2) = y2;
         } else if (row < R) {
           uint16_t* d = out + (size_t)row * Cout + n;
-          if ((Cout & 3) == 0) {
-            if (n < Cout) *reinterpret_cast<uint2*>(d) = y2;
+          if (n + 4 <= Cout) {
+            store8_any(d, y2);
           } else {
 #pragma unroll
-            for (int v = 0; v < 4; ++v)
+            for (int v = 0; v < 3; ++v)
               if (n + v < Cout) d[v] = (uint16_t)f32_to_bf16_bits(y[v]);
           }
         }
@@ -444,19 +444,32 @@ __device__ __forceinline__ void mrconv_tile(char* smem, const MrArgs& a, int row
     }
     if (rows) {
       __syncthreads();
-      // the tile's rows are contiguous in out
-      const int vr = Cout / 8, nv = min(TM, R - row0) * vr;
+      const int vr = (Cout + 7) / 8, nv = min(TM, R - row0) * vr;
       uint16_t* d = out + (size_t)row0 * Cout;
       const int er = kMrThreads / vr, ec = kMrThreads - er * vr;
       int r = tid / vr, c = tid - r * vr;
-      for (int e = tid; e < nv; e += kMrThreads) {
-        *reinterpret_cast<uint4*>(d + (size_t)e * 8) = *reinterpret_cast<const uint4*>(sA + r * lds_row + c * 16);
-        r += er;
-        c += ec;
-        if (c >= vr) {
-          c -= vr;
-          ++r;
+      auto copy = [&](auto&& put) {
+        for (int e = tid; e < nv; e += kMrThreads) {
+          put(e, sA + r * lds_row + c * 16);
+          r += er;
+          c += ec;
+          if (c >= vr) {
+            c -= vr;
+            ++r;
+          }
         }
+      };
+      if ((Cout & 7) == 0) {  // the rows' vectors are contiguous in out
+        copy([&](int e, const char* s) {
+          *reinterpret_cast<uint4*>(d + (size_t)e * 8) = *reinterpret_cast<const uint4*>(s);
+        });
+      } else {
+        copy([&](int, const char* s) {
+          uint16_t* q = d + (size_t)r * Cout + c * 8;
+          if (c * 8 + 8 <= Cout) store16_any(q, *reinterpret_cast<const uint4*>(s));
+          else
+            for (int v = 0; c * 8 + v < Cout; ++v) q[v] = reinterpret_cast<const uint16_t*>(s)[v];
+        });
       }
     }
     } else {

@@ -208,12 +208,21 @@ PACKED = [
     ("lean_ragged", 40, 251, 72, 9, 72, I.BF16),
     ("lean_k40", 35, 300, 40, 40, 48, I.BF16),
     # the lean tile's stores: wider than its LDS rows, rows of no multiple of four or
-    # eight columns, three and four tiles a wave, waves with none
+    # eight columns, one to four tiles a wave, waves with none, 32 and (66 images) 64
+    # nodes
     ("lean_wide_out", 33, 260, 40, 4, 104, I.BF16),
     ("lean_cout_37", 33, 260, 40, 5, 37, I.BF16),
     ("lean_cout_20", 33, 260, 40, 9, 20, I.BF16),
     ("lean_three_tiles", 33, 260, 168, 16, 168, I.BF16),
     ("lean_four_tiles", 33, 260, 136, 9, 200, I.BF16),
+    ("lean_64_nodes", 66, 251, 72, 9, 72, I.BF16),
+    ("lean_64_nodes_cout_99", 66, 251, 56, 9, 99, I.BF16),
+    ("lean_64_nodes_cout_119_wide", 66, 251, 56, 4, 119, I.BF16),
+    ("lean_cout_155", 33, 260, 88, 9, 155, I.BF16),
+    ("lean_cout_190", 33, 260, 96, 4, 190, I.BF16),
+    ("lean_cout_190_wide", 33, 260, 40, 9, 190, I.BF16),
+    ("lean_cout_256", 33, 260, 64, 9, 256, I.BF16),
+    ("lean_C256_cout_203", 33, 260, 256, 5, 203, I.BF16),
     ("lean_fp32", 33, 260, 68, 9, 68, I.F32),
     ("lean_fp32_cout_33", 33, 260, 40, 12, 33, I.F32),
     ("lean_fp32_four_passes", 33, 260, 68, 4, 250, I.F32),
