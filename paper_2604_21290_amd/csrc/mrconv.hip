@@ -46,14 +46,14 @@ __global__ __launch_bounds__(kMrThreads) __attribute__((amdgpu_waves_per_eu(RT *
 // Small grids: workgroup blk computes output-column group blk % ncg (a.col_tiles
 // 16-column tiles) of node tile blk / ncg.  Few workgroups run, so the kernel is
 // not held to three waves per SIMD.
-template <int DT, int RT, int KB, bool ACT = false>
+template <int DT, int RT, int KB, int TPT, bool ACT = false>
 __global__ __launch_bounds__(kMrThreads) void mrconv_cols_kernel(MrArgs a) {
   extern __shared__ __align__(16) char smem[];
   const int nct = (a.Cout + 15) >> 4;
   const int ncg = (nct + a.col_tiles - 1) / a.col_tiles;
   const int blk = blockIdx.x, cg = blk % ncg;
   const int tile0 = cg * a.col_tiles;
-  mrconv_tile<DT, RT, KB, false, false, true, 0, ACT>(smem, a, (blk / ncg) * 16 * RT, tile0,
+  mrconv_tile<DT, RT, KB, false, false, TPT, 0, ACT>(smem, a, (blk / ncg) * 16 * RT, tile0,
                                                           min(nct, tile0 + a.col_tiles));
 }
 
@@ -66,7 +66,7 @@ __global__ __launch_bounds__(kMrThreads) void mrconv_heads_kernel(MrArgs a) {
   mrconv_tile<DT, RT, KB, true>(smem, a, blk * 16 * RT);
 }
 
-template <int DT, int RT, bool HEADS = false, bool COLS = false, int LEAN = 0, bool ACT = false>
+template <int DT, int RT, bool HEADS = false, int COLS = 0, int LEAN = 0, bool ACT = false>
 const void* mrconv_fn_kb(int KB) {
   if constexpr (LEAN > 0) {
     switch (KB) {
@@ -77,10 +77,10 @@ const void* mrconv_fn_kb(int KB) {
     }
   } else if constexpr (COLS) {
     switch (KB) {
-      case 9: return (const void*)&mrconv_cols_kernel<DT, RT, 9, ACT>;
-      case 16: return (const void*)&mrconv_cols_kernel<DT, RT, 16, ACT>;
-      case 32: return (const void*)&mrconv_cols_kernel<DT, RT, 32, ACT>;
-      default: return (const void*)&mrconv_cols_kernel<DT, RT, 64, ACT>;
+      case 9: return (const void*)&mrconv_cols_kernel<DT, RT, 9, COLS, ACT>;
+      case 16: return (const void*)&mrconv_cols_kernel<DT, RT, 16, 1, ACT>;
+      case 32: return (const void*)&mrconv_cols_kernel<DT, RT, 32, 1, ACT>;
+      default: return (const void*)&mrconv_cols_kernel<DT, RT, 64, 1, ACT>;
     }
   } else if constexpr (HEADS) {
     switch (KB) {
@@ -100,10 +100,17 @@ const void* mrconv_fn_kb(int KB) {
 }
 
 // The dense variants' table, with or without the GELU epilogue (a.act_out).
-template <int DT, int RT, bool COLS = false, int LEAN = 0>
+template <int DT, int RT, int COLS = 0, int LEAN = 0>
 const void* mrconv_fn_act(int KB, int act) {
   return act ? mrconv_fn_kb<DT, RT, false, COLS, LEAN, true>(KB)
              : mrconv_fn_kb<DT, RT, false, COLS, LEAN, false>(KB);
+}
+
+// The small grids' variants, with tpt gather tasks in flight per thread.
+template <int DT, int RT>
+const void* mrconv_cols_fn(int KB, int act, int tpt) {
+  return tpt == 1 ? mrconv_fn_act<DT, RT, 1>(KB, act)
+         : tpt == 2 ? mrconv_fn_act<DT, RT, 2>(KB, act) : mrconv_fn_act<DT, RT, 3>(KB, act);
 }
 
 // Gather-only workgroup of the two-pass MRConv: kMrGatherRows nodes.
@@ -207,8 +214,15 @@ hipError_t launch_mrconv_args(const MrArgs& a0, int dt_bf16, int rt, void* split
   const void* fn;
   const int act = a.act_out;
   if (a.col_tiles > 0) {
-    fn = dt_bf16 ? (rt == 2 ? mrconv_fn_act<1, 2, true>(KB, act) : mrconv_fn_act<1, 1, true>(KB, act))
-                 : (rt == 2 ? mrconv_fn_act<0, 2, true>(KB, act) : mrconv_fn_act<0, 1, true>(KB, act));
+    // Gather tasks in flight per thread, of nine loads each (of sixteen and more one:
+    // two or three are slower): three where that saves a round, one where there is
+    // one.  us, three always / so: one image of 196 nodes, C = 512, Cout = 256, bf16
+    // 10.6 / 9.9; C = 252, Cout = 88, fp32 10.6 / 10.2; 1568 nodes, C = 64, Cout = 256, bf16 7.5 / 6.6,
+    // fp32 8.6 / 7.6.
+    const int n = (16 * rt * (C / (dt_bf16 ? 8 : 4)) + kMrThreads - 1) / kMrThreads;
+    const int tpt = (n + 2) / 3 < (n + 1) / 2 ? 3 : n == 1 ? 1 : 2;
+    fn = dt_bf16 ? (rt == 2 ? mrconv_cols_fn<1, 2>(KB, act, tpt) : mrconv_cols_fn<1, 1>(KB, act, tpt))
+                 : (rt == 2 ? mrconv_cols_fn<0, 2>(KB, act, tpt) : mrconv_cols_fn<0, 1>(KB, act, tpt));
   } else if (a.heads > 1) {
     fn = dt_bf16 ? (rt == 2 ? mrconv_fn_kb<1, 2, true>(KB) : mrconv_fn_kb<1, 1, true>(KB))
                  : (rt == 2 ? mrconv_fn_kb<0, 2, true>(KB) : mrconv_fn_kb<0, 1, true>(KB));
@@ -223,17 +237,17 @@ hipError_t launch_mrconv_args(const MrArgs& a0, int dt_bf16, int rt, void* split
     const int nc = !dt_bf16 || nct <= 4 || nct > 12 ? 1 : nct <= 8 ? 2 : 3;
     if (mrconv_smem_bytes(C, k, dt_bf16, 4) <= 65536) {
       if (nc == 2 && rt == 2 && (a.R + 63) / 64 < 256) {
-        fn = mrconv_fn_act<1, 2, false, 2>(KB, act);
+        fn = mrconv_fn_act<1, 2, 0, 2>(KB, act);
       } else {
-        fn = !dt_bf16 ? mrconv_fn_act<0, 4, false, 1>(KB, act)
-             : nc == 1 ? mrconv_fn_act<1, 4, false, 1>(KB, act)
-             : nc == 2 ? mrconv_fn_act<1, 4, false, 2>(KB, act) : mrconv_fn_act<1, 4, false, 3>(KB, act);
+        fn = !dt_bf16 ? mrconv_fn_act<0, 4, 0, 1>(KB, act)
+             : nc == 1 ? mrconv_fn_act<1, 4, 0, 1>(KB, act)
+             : nc == 2 ? mrconv_fn_act<1, 4, 0, 2>(KB, act) : mrconv_fn_act<1, 4, 0, 3>(KB, act);
         return launch_with_smem(fn, dim3((a.R + 63) / 64), block, mrconv_smem_bytes(C, k, dt_bf16, 4),
                                 stream, ev0, ev1, a);
       }
     } else {
-      fn = dt_bf16 ? (rt == 2 ? mrconv_fn_act<1, 2, false, 4>(KB, act) : mrconv_fn_act<1, 1, false, 4>(KB, act))
-                   : (rt == 2 ? mrconv_fn_act<0, 2, false, 1>(KB, act) : mrconv_fn_act<0, 1, false, 1>(KB, act));
+      fn = dt_bf16 ? (rt == 2 ? mrconv_fn_act<1, 2, 0, 4>(KB, act) : mrconv_fn_act<1, 1, 0, 4>(KB, act))
+                   : (rt == 2 ? mrconv_fn_act<0, 2, 0, 1>(KB, act) : mrconv_fn_act<0, 1, 0, 1>(KB, act));
     }
   } else {
     fn = dt_bf16 ? (rt == 2 ? mrconv_fn_act<1, 2>(KB, act) : mrconv_fn_act<1, 1>(KB, act))

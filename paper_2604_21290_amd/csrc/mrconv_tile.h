@@ -72,14 +72,14 @@ template <bool COLS, int LEAN = 0> struct MrBatch {
   static constexpr int NC = COLS ? 1 : LEAN ? LEAN : 4;    // output tiles per wave and pass
 };
 
-template <int DT, bool HEADS, bool COLS = false, int LEAN = 0>
-__device__ __forceinline__ void mr_load_w(uint4 (&bw)[(MrBatch<COLS, LEAN>::KU)][(MrBatch<COLS, LEAN>::NC)],
+template <int DT, bool HEADS, int COLS = 0, int LEAN = 0>
+__device__ __forceinline__ void mr_load_w(uint4 (&bw)[(MrBatch<(COLS > 0), LEAN>::KU)][(MrBatch<(COLS > 0), LEAN>::NC)],
                                           const MrArgs& a, const char* Wb, int w, int p, int s0,
                                           int K2, int Cout, int g, int t, int tile0 = 0,
                                           int tile_end = 0) {
   constexpr int ES = DT ? 2 : 4;
   constexpr int KSTEP = DT ? 32 : 16;
-  constexpr int KU = MrBatch<COLS, LEAN>::KU, NC = MrBatch<COLS, LEAN>::NC;
+  constexpr int KU = MrBatch<(COLS > 0), LEAN>::KU, NC = MrBatch<(COLS > 0), LEAN>::NC;
 #pragma unroll
   for (int c4 = 0; c4 < NC; ++c4) {
     const int n0 = ((COLS ? tile0 : 0) + w + 4 * (NC * p + c4)) * 16;
@@ -122,8 +122,10 @@ __device__ __forceinline__ uint32_t bf16_pair_unsafe(uint32_t w) {
 // written.  Called by all 256 threads.
 // T3: three tasks per thread in flight instead of two (a caller with registers
 // to spare takes the 32-node tile's 768 tasks of C = 192 in one round).
+// COLS > 0: that many (small grids, whose workgroups, about two per CU, have the
+// registers; the launcher chooses).
 // MONLY: only m_i is written (to dst + r * dst_stride).
-template <int DT, int KB, bool T3 = false, int LEAN = 0, bool COLS = false, bool MONLY = false>
+template <int DT, int KB, bool T3 = false, int LEAN = 0, int COLS = 0, bool MONLY = false>
 __device__ __forceinline__ void mr_gather_rows(const MrArgs& a, int row0, int TM,
                                                const int32_t* sIdx, char* dst, size_t dst_stride) {
   constexpr int ES = DT ? 2 : 4;
@@ -134,10 +136,8 @@ __device__ __forceinline__ void mr_gather_rows(const MrArgs& a, int row0, int TM
   // Each task is one (node, 16-byte channel vector); with a small neighbour
   // bucket two tasks keep their loads in flight together.
   constexpr int KG = KB < 16 ? KB : 16;    // neighbour loads in flight per group
-  // tasks per thread per iteration (a small grid's workgroups, about two per CU,
-  // have the registers for three of nine loads; of sixteen, two or three are
-  // slower: 3 x 513, C = 204, k = 12, fp32 15.8 -> 25.1 us)
-  constexpr int TPT = COLS ? (KB <= 9 ? 3 : 1) : KB <= 9 && !LEAN ? (T3 ? 3 : 2) : 1;
+  // tasks per thread per iteration
+  constexpr int TPT = COLS ? COLS : KB <= 9 && !LEAN ? (T3 ? 3 : 2) : 1;
   const int ntask = TM * CG;
   // Task e is vector e % CG of node e / CG; in bf16 a thread's tasks, kMrThreads
   // apart, advance (node, vector) by a fixed step and one carry, and the tile's nodes
@@ -276,7 +276,7 @@ __device__ __forceinline__ void mr_gather_tile(const MrArgs& a, int blk, int TM,
   }
   __syncthreads();
   const size_t stride = (size_t)(DT ? 1 : 2) * a.C * ES;
-  mr_gather_rows<DT, KB, false, 0, false, DT == 1>(a, row0, TM, sIdx, static_cast<char*>(xcat) + row0 * stride,
+  mr_gather_rows<DT, KB, false, 0, 0, DT == 1>(a, row0, TM, sIdx, static_cast<char*>(xcat) + row0 * stride,
                                                    stride);
 }
 
@@ -287,7 +287,7 @@ __device__ __forceinline__ void mr_gather_tile(const MrArgs& a, int blk, int TM,
 // the layer's tiles), the column group of a small grid.
 // ACT: GELU on each output before its rounding (a.act_out; compiled in only
 // for the full block's update, so the other updates carry none of its code).
-template <int DT, int RT, int KB, bool HEADS = false, bool T3 = false, bool COLS = false,
+template <int DT, int RT, int KB, bool HEADS = false, bool T3 = false, int COLS = 0,
           int LEAN = 0, bool ACT = false>
 __device__ __forceinline__ void mrconv_tile(char* smem, const MrArgs& a, int row0, int tile0 = 0,
                                             int tile_end = 0) {
@@ -318,7 +318,7 @@ __device__ __forceinline__ void mrconv_tile(char* smem, const MrArgs& a, int row
   const char* Wb = static_cast<const char*>(a.W);
   // output tiles past Cout are never loaded: their operands stay zero (their
   // results are not stored either)
-  constexpr int KU = MrBatch<COLS, LEAN>::KU, NC = MrBatch<COLS, LEAN>::NC;
+  constexpr int KU = MrBatch<(COLS > 0), LEAN>::KU, NC = MrBatch<(COLS > 0), LEAN>::NC;
   uint4 bw[KU][NC] = {};
   const int T0 = COLS ? tile0 : 0, TE = COLS ? tile_end : NCT;
   if (T0 + w < TE) mr_load_w<DT, HEADS, COLS, LEAN>(bw, a, Wb, w, 0, 0, K2, Cout, g, t, tile0, tile_end);

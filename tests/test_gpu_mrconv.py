@@ -281,6 +281,9 @@ def test_gather_edge_values(case):
     (1, 2048, 96, 9, 200, I.BF16),     # the most nodes of column groups, in 16-node tiles
     (1, 2047, 72, 9, 640, I.BF16),     # ... too many groups for 16: 32-node tiles
     (5, 100, 320, 9, 328, I.F32),      # wide fp32 rows: 16 nodes by LDS
+    # one to five gather tasks per thread, the last of them partly past the tile
+    (1, 100, 64, 9, 72, I.F32), (1, 100, 136, 5, 72, I.BF16), (1, 130, 232, 9, 80, I.BF16),
+    (1, 100, 252, 9, 88, I.F32), (2, 70, 296, 9, 72, I.F32), (3, 60, 512, 9, 136, I.BF16),
 ])
 def test_column_groups_edges(B, N, C, k, Co, dt):
     """Small grids, whose output columns are split over workgroups, in tiles of 16
