@@ -196,6 +196,11 @@ __device__ __forceinline__ void mr_gather_rows(const MrArgs& a, int row0, int TM
           const uint32_t jo = (uint32_t)nb[q][tt < k ? tt : 0];
           raw[q][u] = *reinterpret_cast<const uint4*>(kbase[q] + ((size_t)jo << 4));
         }
+      // Past 16 neighbours the scheduler would start the bf16 maxima after eight of a
+      // group's loads and issue the others behind them (6272 nodes, C = 192, k = 24:
+      // 14.8 us so, @B1@ with all in flight first).  The lists of one group, and the
+      // column groups, which have fewer workgroups, are faster left to it.
+      if constexpr (DT && KB > 16 && !COLS) __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
       for (int q = 0; q < TPT; ++q)
 #pragma unroll
@@ -218,7 +223,7 @@ __device__ __forceinline__ void mr_gather_rows(const MrArgs& a, int row0, int TM
       for (int q = 0; q < TPT; ++q)
 #pragma unroll
         for (int i = 0; i < 4; ++i) unsafe |= bf16_pair_unsafe(mp[q][i]);
-      if (__any(unsafe != 0)) {  // rare: infinities, NaN, or magnitudes from 2^121 on
+      if (__builtin_expect(__any(unsafe != 0), 0)) {  // rare: infinities, NaN, or magnitudes from 2^121 on
 #pragma unroll
         for (int q = 0; q < TPT; ++q) {
           // the task's addresses again: kept until here they took the block kernel's
