@@ -105,9 +105,12 @@ __global__ __launch_bounds__(G::kThreads) __attribute__((amdgpu_waves_per_eu(4, 
   const uint16_t* bias = static_cast<const uint16_t*>(a.bias);
   const uint16_t* res = static_cast<const uint16_t*>(a.residual);
   uint16_t* out = static_cast<uint16_t*>(a.out);
-  // 16-byte accesses to out and the residual need aligned rows; else by element
-  const bool vec = (Cout & 7) == 0 &&
-                   ((reinterpret_cast<uintptr_t>(out) | reinterpret_cast<uintptr_t>(res)) & 15) == 0;
+  // out and the residual are accessed 16 bytes at a time whatever their rows'
+  // alignment; only a row's last columns, fewer than eight, go one by one (before,
+  // all did where rows were not whole vectors, us: 100352 x 160 -> 157 45.5 -> 24.5,
+  // 25088 x 640 -> 637 47.0 -> 31.6; 2-byte stores of 16 neighbouring columns, register-staged
+  // kernel, 26.1 and 38.2)
+  const bool vec = n + 8 <= Cout;
   float bn[8];
 #pragma unroll
   for (int v = 0; v < 8; ++v) bn[v] = bias ? bf16_bits_to_f32(bias[min(n + v, Cout - 1)]) : 0.f;
@@ -115,8 +118,7 @@ __global__ __launch_bounds__(G::kThreads) __attribute__((amdgpu_waves_per_eu(4, 
   if (RES && vec) {
 #pragma unroll
     for (int p = 0; p < NP; ++p)
-      rv[p] = *reinterpret_cast<const uint4*>(res + (size_t)min(row0 + p * RPP, R - 1) * Cout +
-                                              min(n, Cout - 8));
+      rv[p] = load16_any(res + (size_t)min(row0 + p * RPP, R - 1) * Cout + n);
   }
 
   f32x4 acc[TM][TN];
@@ -179,7 +181,7 @@ __global__ __launch_bounds__(G::kThreads) __attribute__((amdgpu_waves_per_eu(4, 
 #pragma unroll
         for (int v = 0; v < 8; ++v) y[v] += f[v];
       }
-      *reinterpret_cast<uint4*>(out + o) = pack_bf16x8(y);
+      store16_any(out + o, pack_bf16x8(y));
     } else {
 #pragma unroll
       for (int v = 0; v < 8; ++v)

@@ -99,6 +99,9 @@ __device__ __forceinline__ void dma_wait_barrier() {
 // splits those that cross a line)
 typedef uint32_t u32x2_any __attribute__((ext_vector_type(2), aligned(2), may_alias));
 typedef uint32_t u32x4_any __attribute__((ext_vector_type(4), aligned(2), may_alias));
+__device__ __forceinline__ uint4 load16_any(const void* p) {
+  return __builtin_bit_cast(uint4, *static_cast<const u32x4_any*>(p));
+}
 __device__ __forceinline__ void store16_any(void* p, uint4 v) {
   *static_cast<u32x4_any*>(p) = __builtin_bit_cast(u32x4_any, v);
 }

@@ -198,7 +198,7 @@ __device__ __forceinline__ void mr_gather_rows(const MrArgs& a, int row0, int TM
         }
       // Past 16 neighbours the scheduler would start the bf16 maxima after eight of a
       // group's loads and issue the others behind them (6272 nodes, C = 192, k = 24:
-      // 14.8 us so, @B1@ with all in flight first).  The lists of one group, and the
+      // 14.8 us so, 14.2 with all in flight first).  The lists of one group, and the
       // column groups, which have fewer workgroups, are faster left to it.
       if constexpr (DT && KB > 16 && !COLS) __builtin_amdgcn_sched_barrier(0);
 #pragma unroll

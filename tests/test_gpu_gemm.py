@@ -28,6 +28,14 @@ CASES = [
     ("32x64_ragged", 33, 264, 65, 0, True, True, 0),
     ("32x64_two_k_stages", 65, 128 + 8, 72, 1, False, True, 0),
     ("32x64_one_element", 1, 8, 1, 0, True, True, 0),
+    # rows of every alignment: 2, 4 and 8 bytes, out and residual at an odd element
+    ("128x128_odd_rows_unaligned", 128 * 192 + 7, 40, 255, 0, True, True, 3),
+    ("128x128_even_rows", 128 * 192 - 9, 104, 250, 1, False, True, 2),
+    ("128x64_odd_rows_unaligned", 128 * 200 + 5, 80, 157, 0, True, True, 5),
+    ("64x64_odd_rows_unaligned", 1300, 192, 443, 1, True, True, 7),
+    ("64x64_whole_rows_unaligned", 1300, 192, 448, 0, True, True, 5),
+    ("32x64_odd_rows", 333, 200, 61, 0, True, True, 1),
+    ("32x64_seven_columns", 40, 64, 7, 0, True, False, 3),
 ]
 
 
