@@ -213,19 +213,26 @@ hipError_t launch_cfg(const GemmArgs& a, hipStream_t stream, hipEvent_t ev0, hip
 //   128 x 64 (8)        23.8          16.4            9.8 *         8.5           7.5
 //   64 x 64 (4)         24.6          16.6           10.9           8.0 *         7.0
 //   32 x 64 (4)         32.6          21.1           11.6           8.9           5.4 *
-// (* the tile the rule takes: 490, 490, 588, 490 and 21 of them).  Fewer than one
-// 64 x 64 tile per CU with 1 KB of K or more: 8 waves and 256 bytes of K per stage
-// (3136x1280x320 10.1 -> 8.5, 2208x976x264 8.5 -> 7.3; 3136x320x320 no gain;
-// 784x640x2560, two per CU, 9.4 -> 12.5).  The tiles of
-// 32 rows take 256 bytes of K per stage: on a grid of a few workgroups each
-// stage's round trip to memory shows.
+// (* the tile the rule takes: 490, 490, 588, 490 and 21 of them).  128 x 128 tiles
+// that just pass one round of two per CU (513 to 640) leave most of the second idle:
+// 128 x 64 where a GELU or padded columns weigh (25088x80x320 GELU 16.0 -> 13.7,
+// 25088x320x320 15.6 -> 14.8; 12544x192x768 13.0 -> 13.2).  64 x 64 tiles of 1 KB of K
+// or more, up to two per CU: 8 waves and 256 bytes of K per stage, twice the bytes in
+// flight, which operands that come from memory need (cached / not, K per stage 128 ->
+// 256 bytes: 6272x1280x320 12.1, 20.0 -> 11.6, 15.5; 3136x2560x640 25.4, 34.4 -> 19.6,
+// 24.2; 6272x768x192 8.3, 13.3 -> 8.3, 10.7; the register-staged kernel with three
+// stages in flight 17.1, 18.8; 30.2, 31.1; 10.9, 12.1; 784x640x2560, 520 tiles, 9.4 ->
+// 12.5).  The tiles of 32 rows take 256 bytes of K per stage: on a grid of a few
+// workgroups each stage's round trip to memory shows.
 hipError_t launch_gemm_dma(const GemmArgs& a, hipStream_t stream, hipEvent_t ev0, hipEvent_t ev1) {
   auto tiles = [&](int bm, int bn) { return (long)((a.R + bm - 1) / bm) * ((a.Cout + bn - 1) / bn); };
   const int pad64 = (a.Cout + 63) / 64, pad128 = 2 * ((a.Cout + 127) / 128);
-  if (tiles(128, 128) >= 384 && 4 * pad128 <= 5 * pad64)
+  const long t128 = tiles(128, 128);
+  const bool one_more = t128 > 512 && t128 <= 640 && (a.act_out || pad128 > pad64);
+  if (t128 >= 384 && 4 * pad128 <= 5 * pad64 && !one_more)
     return launch_cfg<DmaCfg<128, 128, 128, 4, 2>>(a, stream, ev0, ev1);
   if (tiles(128, 64) >= 384) return launch_cfg<DmaCfg<128, 64, 128, 4, 2>>(a, stream, ev0, ev1);
-  if (tiles(64, 64) >= 128 && tiles(64, 64) < 256 && a.K >= 512)
+  if (tiles(64, 64) >= 128 && tiles(64, 64) <= 512 && a.K >= 512)
     return launch_cfg<DmaCfg<64, 64, 256, 4, 2>>(a, stream, ev0, ev1);
   if (tiles(64, 64) >= 128) return launch_cfg<DmaCfg<64, 64, 128, 2, 2>>(a, stream, ev0, ev1);
   return launch_cfg<DmaCfg<32, 64, 256, 1, 4>>(a, stream, ev0, ev1);

@@ -25,6 +25,11 @@ CASES = [
     ("64x64_aligned_8_bytes", 1300, 64, 456, 0, True, False, 4),
     ("64x64_long_k", 1999, 520, 257, 0, True, True, 0),
     ("64x64_long_k_gelu", 2208, 976, 264, 1, False, True, 0),
+    ("64x64_long_k_two_per_cu", 64 * 32 - 3, 520, 64 * 16 - 8, 0, True, True, 0),
+    ("64x64_past_two_per_cu", 64 * 32 + 1, 520, 64 * 16, 0, False, True, 0),
+    ("128x64_padded_second_round", 128 * 171 + 1, 40, 320, 0, True, True, 0),
+    ("128x64_gelu_second_round", 128 * 257, 24, 256, 1, False, True, 0),
+    ("128x128_second_round", 128 * 257, 24, 256, 0, True, True, 0),
     ("32x64_ragged", 33, 264, 65, 0, True, True, 0),
     ("32x64_two_k_stages", 65, 128 + 8, 72, 1, False, True, 0),
     ("32x64_one_element", 1, 8, 1, 0, True, True, 0),
