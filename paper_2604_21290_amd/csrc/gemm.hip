@@ -1,5 +1,6 @@
 // Tiled MFMA GEMM for the fully connected layers of the path, staged through
-// registers: fp32, and bf16 with a GELU on A (other bf16 layers: gemm_dma.hip)
+// registers: fp32, bf16 with a GELU on A, and the bf16 layers of short rows that it is
+// faster at (gemm_prefers_registers; the others: gemm_dma.hip)
 //   out[R, Cout] = act_out(act_in(A)[R, K] W[Cout, K]^T + b) + residual
 //   * the MRConv update over materialised [x | m] rows for wide channels
 //     (Sec. II-A Eq. 3; the W_x / W_m split of Sec. IV-C2 is the two halves of
@@ -263,20 +264,42 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(BM == 1
   }
 }
 
-// v: act_out + 2 act_in (fp32), or act_out + 4 (bf16 with a GELU on A).
+// v: act_out + 2 act_in, + 4 in bf16.
 template <int BM, int STEP, int NW = 4>
 const void* gemm_fn(int v) {
-  static const void* const fns[6] = {
+  static const void* const fns[8] = {
       (const void*)&gemm_nt_kernel<0, 0, 0, BM, STEP, NW>, (const void*)&gemm_nt_kernel<0, 0, 1, BM, STEP, NW>,
       (const void*)&gemm_nt_kernel<0, 1, 0, BM, STEP, NW>, (const void*)&gemm_nt_kernel<0, 1, 1, BM, STEP, NW>,
+      (const void*)&gemm_nt_kernel<1, 0, 0, BM, STEP, NW>, (const void*)&gemm_nt_kernel<1, 0, 1, BM, STEP, NW>,
       (const void*)&gemm_nt_kernel<1, 1, 0, BM, STEP, NW>, (const void*)&gemm_nt_kernel<1, 1, 1, BM, STEP, NW>};
   return fns[v];
 }
 
+// bf16 layers without a GELU on A that these tiles compute faster than those of
+// gemm_dma.hip; the results are the same.  They hold a short row in one stage (K up
+// to 96 in exactly its bytes) and store two bytes a lane, which neither odd rows nor
+// few of them slow down.  us, direct loads to LDS / here:
+//   a few rows and a GELU (a lane there holds eight columns of a row, here one):
+//     1 x 192 -> 768 5.1 / 4.2, 1 x 640 -> 640 6.4 / 6.1; without GELU 4.2 / 4.2, 5.6 / 6.1;
+//   rows of no multiple of eight columns with a residual: 6272 x 160 -> 157 6.8 / 5.7,
+//     100352 x 96 -> 100 22.0 / 17.6; without, on many rows: 100352 x 8 -> 37 9.6 / 7.8,
+//     25088 x 96 -> 100 6.1 / 5.7 (6272 5.6 / 4.3 before they were stored 16 bytes a
+//     lane, 4.4 / 4.4 since);
+//   many short rows to fewer columns than a tile has: 100352 x 96 -> 48 9.3 / 8.1;
+//   a second stage of K = 65 .. 95 that is half zeros, with a GELU: 25088 x 80 -> 320 13.7
+//     / 13.0, 100352 40.3 / 38.7; without: 100352 33.9 / 35.2.
+static bool gemm_prefers_registers(const GemmArgs& a) {
+  if (a.A2) return false;
+  const bool odd = (a.Cout & 7) != 0;
+  return (a.act_out && a.R <= 16 && a.K <= 640) || (odd && a.residual && a.K <= 256) ||
+         (odd && a.K <= 128 && a.R >= 20000) || (a.Cout < 64 && a.K <= 96 && a.R >= 32768) ||
+         (a.act_out && a.K > 64 && a.K < 96 && a.R >= 20000);
+}
+
 hipError_t launch_gemm_nt(const GemmArgs& a, int dt_bf16, hipStream_t stream, hipEvent_t ev0,
                           hipEvent_t ev1) {
-  if (dt_bf16 && !a.act_in) return launch_gemm_dma(a, stream, ev0, ev1);
-  const int v = (dt_bf16 ? 4 : a.act_in ? 2 : 0) + (a.act_out ? 1 : 0);
+  if (dt_bf16 && !a.act_in && !gemm_prefers_registers(a)) return launch_gemm_dma(a, stream, ev0, ev1);
+  const int v = (dt_bf16 ? 4 : 0) + (a.act_in ? 2 : 0) + (a.act_out ? 1 : 0);
   const size_t rowb = (size_t)a.K * (dt_bf16 ? 2 : 4);
   // large tiles once they alone give every CU a tile and K is long
   const long tiles128 = (long)((a.R + 127) / 128) * ((a.Cout + 127) / 128);

@@ -1,8 +1,8 @@
 // bf16 tiled MFMA GEMM whose operands reach LDS by direct loads:
 //   out[R, Cout] = act_out(A[R, K] W[Cout, K]^T + b) + residual
-// Every bf16 layer without a GELU on its input runs here: FC1, FC2 + residual,
-// the FFN, the GEMM pass of the two-pass MRConv and gl_linear (gemm.hip has
-// fp32 and the GELU on A).
+// The bf16 layers without a GELU on their input run here: FC1, FC2 + residual, the
+// FFN, the GEMM pass of the two-pass MRConv and gl_linear (gemm.hip has fp32, the
+// GELU on A and some layers of short rows).
 //   - Staging: global_load_lds moves 16 bytes per lane from a row of A or W
 //     straight into LDS, so a stage in flight holds no registers and is not
 //     written by ds_write.  A wave's load fills 1024 consecutive bytes of LDS, so

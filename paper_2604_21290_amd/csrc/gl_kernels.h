@@ -148,7 +148,7 @@ hipError_t launch_expand_heads(const void* Wh, void* Wd, int C, int heads, int d
                                hipStream_t stream);
 hipError_t launch_gemm_nt(const GemmArgs& a, int dt_bf16, hipStream_t stream, hipEvent_t ev0,
                           hipEvent_t ev1);
-// Its bf16 layers without a GELU on A (gemm_dma.hip); launch_gemm_nt calls it.
+// Most of its bf16 layers without a GELU on A (gemm_dma.hip); launch_gemm_nt calls it.
 hipError_t launch_gemm_dma(const GemmArgs& a, hipStream_t stream, hipEvent_t ev0, hipEvent_t ev1);
 
 // The tail of a full block in one launch (mlp.hip), for the shapes it is faster

@@ -30,6 +30,17 @@ CASES = [
     ("128x64_padded_second_round", 128 * 171 + 1, 40, 320, 0, True, True, 0),
     ("128x64_gelu_second_round", 128 * 257, 24, 256, 1, False, True, 0),
     ("128x128_second_round", 128 * 257, 24, 256, 0, True, True, 0),
+    # layers that are staged through registers, and their neighbours that are not
+    ("registers_16_rows_gelu", 16, 640, 200, 1, False, True, 0),
+    ("17_rows_gelu", 17, 640, 200, 1, False, True, 0),
+    ("16_rows_gelu_long_k", 16, 648, 200, 1, False, True, 0),
+    ("registers_odd_residual", 1000, 256, 157, 0, True, True, 1),
+    ("odd_residual_long_k", 1000, 264, 157, 0, True, True, 1),
+    ("registers_odd_many_rows", 20000, 128, 20, 0, False, True, 0),
+    ("odd_many_rows_long_k", 20000, 136, 20, 0, False, True, 0),
+    ("registers_few_columns", 32768, 96, 56, 0, True, True, 0),
+    ("registers_half_stage_gelu", 20000, 88, 128, 1, False, True, 0),
+    ("whole_stage_gelu", 20000, 64, 128, 1, False, True, 0),
     ("32x64_ragged", 33, 264, 65, 0, True, True, 0),
     ("32x64_two_k_stages", 65, 128 + 8, 72, 1, False, True, 0),
     ("32x64_one_element", 1, 8, 1, 0, True, True, 0),
