@@ -85,13 +85,16 @@ EDGE = [
     ("wide_C_bf16", 1, 40, None, 1024, 9, 4, I.BF16, "unit"),
     ("unnormalised_fp32", 3, 196, None, 192, 9, 2, I.F32, "normal"),
     ("KK_33_R4", 1, 196, None, 64, 11, 3, I.BF16, "normal"),
-    # streamed-key kernel (M > 256): ragged last chunk, widest rows, fp32
-    ("stream_ragged_M333", 2, 90, 333, 96, 16, 2, I.BF16, "normal"),
-    ("stream_wide_C768_bf16", 1, 70, 300, 768, 9, 1, I.BF16, "unit"),
-    ("stream_wide_C384_fp32", 1, 70, 300, 384, 9, 2, I.F32, "normal"),
-    ("stream_C160_R4", 2, 64, 784, 160, 16, 4, I.BF16, "unit"),
-    ("stream_fp32_C96", 1, 130, 3136, 96, 16, 2, I.F32, "normal"),
-    # more than 256 workgroups of 128 rows: the four-wave form of the narrow rows
+    # more than 256 keys on small grids (up to 512 tiles of 16 rows in any width): the
+    # in-register kernel in chunks of 256 keys, the last one ragged; the widest
+    # rows that larger grids stream; fp32
+    ("small_grid_M333", 2, 90, 333, 96, 16, 2, I.BF16, "normal"),
+    ("small_grid_C768_bf16", 1, 70, 300, 768, 9, 1, I.BF16, "unit"),
+    ("small_grid_C384_fp32", 1, 70, 300, 384, 9, 2, I.F32, "normal"),
+    ("small_grid_C160_R4", 2, 64, 784, 160, 16, 4, I.BF16, "unit"),
+    ("small_grid_fp32_C96", 1, 130, 3136, 96, 16, 2, I.F32, "normal"),
+    # streamed, more than 256 workgroups of 128 rows: the four-wave form of the
+    # narrow rows
     ("stream_four_waves_B33", 33, 1000, 400, 64, 9, 2, I.BF16, "normal"),
     # LDS-staged wide kernel (bf16, C >= 256, M <= 256): key-row buckets 64 / 128 /
     # 224 / 256, a partial last stage (C = 520), K' = 64, one query row
@@ -220,6 +223,76 @@ def test_pool_edges():
             assert np.array_equal(got, x.value)
 
 
+# -- the streamed kernel --------------------------------------------------------------
+def _streams(B, N):
+    """Whether builds against more than 256 keys are streamed on this grid: past
+    1024 tiles of 16 rows all are, up to 512 none (up to 256 streamed workgroups)."""
+    tiles = B * ((N + 15) // 16)
+    assert tiles > 1024 or tiles <= 512
+    return tiles > 1024
+
+
+STREAM = [
+    # label, B, N, M, C, k, d, dtype: key counts one past and far from a chunk's
+    # edge and the most of them, every number of contraction steps of either type
+    # (C padded up to 2, 3, 4, 6, 8, 12, 16, 20 or 24), each list length
+    ("M257_KK64", 17, 970, 257, 32, 16, 4, I.BF16),
+    ("ragged_M333", 12, 1390, 333, 96, 16, 2, I.BF16),
+    ("max_M_KK64", 11, 1500, 4096, 16, 16, 4, I.BF16),
+    ("max_M_fp32", 11, 1500, 4096, 8, 8, 8, I.F32),
+    ("C160_KK64", 33, 510, 784, 160, 16, 4, I.BF16),
+    ("fp32_C96_M3136", 17, 970, 3136, 96, 16, 2, I.F32),
+    ("C104", 33, 500, 300, 104, 9, 1, I.BF16),
+    ("C256", 33, 500, 300, 256, 9, 2, I.BF16),
+    ("C384", 33, 500, 300, 384, 9, 4, I.BF16),
+    ("C488", 33, 500, 280, 488, 9, 1, I.BF16),
+    ("C640", 33, 500, 260, 640, 16, 2, I.BF16),
+    ("C768", 33, 500, 300, 768, 9, 1, I.BF16),
+    ("fp32_C36", 33, 500, 300, 36, 9, 1, I.F32),
+    ("fp32_C64", 33, 500, 300, 64, 9, 4, I.F32),
+    ("fp32_C128", 33, 500, 300, 128, 9, 1, I.F32),
+    ("fp32_C192", 33, 500, 300, 192, 9, 2, I.F32),
+    ("fp32_C252", 33, 500, 300, 252, 9, 1, I.F32),
+    ("fp32_C320", 33, 500, 300, 320, 9, 4, I.F32),
+    ("fp32_C384", 33, 500, 300, 384, 9, 2, I.F32),
+]
+
+
+@pytest.mark.parametrize("case", STREAM, ids=[c[0] for c in STREAM])
+def test_knn_streamed(case):
+    """Other keys than queries, on grids past 1024 tiles of 16 rows."""
+    require_gpu()
+    from paper_2604_21290_amd import api
+    label, B, N, M, C, k, d, dt = case
+    assert _streams(B, N) and M > 256, label
+    seed = zlib.crc32(label.encode()) % 10000
+    x = I.random_features(seed, B, N, C, dt, unit=False)
+    keys = I.random_features(seed + 1, B, M, C, dt, unit=False)
+    _say("streamed", label)
+    idx = api.knn_graph(to_dev(x), k, d, keys=to_dev(keys)).cpu().numpy()
+    rows = np.unique(np.linspace(0, N - 1, 48).astype(int))
+    for b in (0, B // 2, B - 1):
+        D = O.knn_distances(x.value[b:b + 1], keys.value[b:b + 1], rows=rows)
+        check_idx(idx[b:b + 1], D, k, d, rows=rows, label=f"{label} image {b}")
+
+
+@pytest.mark.parametrize("B,N,C,dt", [(17, 970, 64, I.BF16), (17, 970, 200, I.F32), (1, 970, 64, I.BF16)])
+def test_knn_many_keys_duplicates_and_zero_rows(B, N, C, dt):
+    """Zero query and key rows and duplicated keys among more than 256, streamed
+    and in-register: ties go to the lower index."""
+    require_gpu()
+    g = np.random.default_rng(17)
+    a = g.standard_normal((B, N, C))
+    kv = g.standard_normal((B, 333, C))
+    a[:, ::7] = 0.0
+    kv[:, 10] = 0.0
+    kv[:, 300:320] = kv[:, 0:20]
+    rows = np.unique(np.concatenate([np.arange(0, 70, 7), g.choice(N, 60, replace=False)]))
+    for d in (1, 3):
+        _say("many keys dup/zero", B, N, C, dt, d,
+             _knn_case(I.store(a, dt), 9, d, I.store(kv, dt), rows=rows, label=f"dup d={d}"))
+
+
 # -- one lane's keys nearest ---------------------------------------------------------
 ONE_LANE = [
     # label, B, N, M, C, k, d, dtype: the kernel that builds the graph
@@ -234,8 +307,11 @@ ONE_LANE = [
     ("resident_r1", 8, 3136, 196, 80, 9, 1, I.BF16),
     ("resident_r2", 8, 3136, 208, 64, 9, 2, I.BF16),
     ("resident_r4_16_tiles", 8, 3136, 256, 40, 16, 4, I.BF16),
-    ("stream_r1", 1, 130, 700, 96, 9, 1, I.BF16),
-    ("stream_r4_fp32", 1, 65, 520, 52, 12, 4, I.F32),
+    ("tile_r1_three_chunks", 1, 130, 700, 96, 9, 1, I.BF16),
+    ("tile_r4_fp32_three_chunks", 1, 65, 520, 52, 12, 4, I.F32),
+    ("stream_r1", 17, 970, 700, 96, 9, 1, I.BF16),
+    ("stream_r2", 17, 970, 600, 200, 9, 3, I.BF16),
+    ("stream_r4_fp32", 17, 970, 520, 52, 12, 4, I.F32),
 ]
 
 
@@ -248,6 +324,8 @@ def test_nearest_keys_in_one_lane(case):
     require_gpu()
     from paper_2604_21290_amd import api
     label, B, N, M, C, k, d, dt = case
+    if M > 256:
+        assert _streams(B, N) == label.startswith("stream"), label
     g = np.random.default_rng(M + C)
     u = g.standard_normal(C)
     u /= np.linalg.norm(u)
@@ -292,7 +370,7 @@ def test_stream_and_tile_agree(case):
     require_gpu()
     from paper_2604_21290_amd import api
     label, B, N, C, k, d, dt = case
-    assert B * ((N + 15) // 16) > 1024 >= (N + 15) // 16
+    assert _streams(B, N) and not _streams(1, N)
     x = I.random_features(N + C, B, N, C, dt, unit=False)
     xd = to_dev(x)
     _say("stream and tile", label)
@@ -352,7 +430,7 @@ def test_non_finite_rows_by_grid(case):
     require_gpu()
     from paper_2604_21290_amd import api
     label, B, N, C, k, d, dt = case
-    assert B * ((N + 15) // 16) > 1024 >= (N + 15) // 16 and N > 256
+    assert _streams(B, N) and not _streams(1, N) and N > 256
     g = np.random.default_rng(N)
     x = to_dev(I.random_features(N + C, B, N, C, dt, unit=False))
     bad = torch.from_numpy(g.random((B, N)) < 0.1).cuda()
