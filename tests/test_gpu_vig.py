@@ -451,3 +451,58 @@ def test_vig_tail(case):
     torch.cuda.synchronize()
     la.close()
     assert torch.equal(out, x), (label, "standard")
+
+
+def _stored_tail(x, s, p):
+    """The tail of a block layer by layer: each layer a launch that stores its rows."""
+    from paper_2604_21290_amd import api
+    y = api.linear(s, p["W_out"], p.get("b_out"), residual=x)
+    h = api.linear(y, p["W_1"], p.get("b_1"), 0, 1)
+    return api.linear(h, p["W_2"], p.get("b_2"), residual=y)
+
+
+@pytest.mark.parametrize("case", TAIL, ids=[c[0] for c in TAIL])
+def test_vig_tail_equals_layers(case):
+    """The one-launch tail against its three layers on the sigma(U~) that the block
+    left at the start of its workspace: bit for bit."""
+    require_gpu()
+    from paper_2604_21290_amd import api
+    label, B, H, W, C, r, bias = case
+    w = I.Workload(label, B, H, W, C, 4, (1,), I.BF16, pool_r=r, seed=67)
+    x = to_dev(I.make_features(w))
+    p = _dev_params(I.make_vig_params(w, 0, bias=bias))
+    u = api.linear(x, p["W_in"], p.get("b_in"))
+    idx = api.knn_graph(u, w.k, 1, keys=api.pool_keys(u, H, W, r) if r > 1 else None)
+    ws = api.vig_workspace(x, w.k, **_grid(w))
+    la = api.Lookahead(torch.cuda.current_stream(), torch.cuda.Stream())
+    _say("vig tail layers", label)
+    out, _ = la.vig_block(x, idx, p, ws, **_grid(w))
+    torch.cuda.synchronize()
+    la.close()
+    s = ws[:x.numel() * 2].view(torch.bfloat16).view(x.shape).clone()
+    want = _stored_tail(x, s, p)
+    torch.cuda.synchronize()
+    assert torch.equal(out, want), label
+
+
+@pytest.mark.parametrize("B,N,C", [(84, 196, 192), (103, 160, 136)])
+def test_vig_block_past_the_tail_rule(B, N, C):
+    """Past 16384 rows of more than 128 channels the layers run one by one: an
+    image's block does not hang on the batch it is in."""
+    require_gpu()
+    from paper_2604_21290_amd import api
+    w = I.Workload("rule", B, N, 1, C, 9, (1,), I.BF16, seed=71)
+    assert B * N > 16384 >= N
+    x = to_dev(I.make_features(w))
+    p = _dev_params(I.make_vig_params(w, 0, bias=True))
+    u = api.linear(x, p["W_in"], p.get("b_in"))
+    idx = api.knn_graph(u, w.k, 1)
+    la = api.Lookahead(torch.cuda.current_stream(), torch.cuda.Stream())
+    _say("vig block past the rule", B, N, C)
+    out, _ = la.vig_block(x, idx, p, api.vig_workspace(x, w.k, **_grid(w)), **_grid(w))
+    for b in (0, B - 1):
+        xb = x[b:b + 1].contiguous()
+        one, _ = la.vig_block(xb, idx[b:b + 1].contiguous(), p, api.vig_workspace(xb, w.k))
+        torch.cuda.synchronize()
+        assert torch.equal(one[0], out[b]), (B, N, C, b)
+    la.close()
