@@ -25,6 +25,7 @@
 //   - act_in is applied to A's elements as they are staged (fp32, rounded back
 //     to the storage type, as if the caller had stored sigma(A)).
 //   - Epilogue in fp32: + bias, act_out, + residual, rounded once.
+#include "gemm_index.h"
 #include "gl_device.h"
 #include "gl_kernels.h"
 
@@ -117,7 +118,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(BM == 1
   auto gload = [&](int q, int s) {
 #pragma unroll
     for (int i = 0; i < kGmVec; ++i) {
-      const int off = s * kGmStep + slot[i] < rowb ? s * kGmStep : 0;
+      const int off = gemm_slot_offset(s, kGmStep, slot[i], rowb);
       ra[q][i] = *reinterpret_cast<const u32x4*>(ag[i] + off);
       rb[q][i] = *reinterpret_cast<const u32x4*>(bg[i] + off);
     }

@@ -82,3 +82,35 @@ def test_bf16_tiles(case):
     check_close(from_dev(out).value, ref, I.BF16, label, mag=1.13 * mag, n_terms=K)
     rest = torch.cat([guard[:off], guard[off + R * Co:]])
     assert bool((rest == 7.0).all()), (label, "wrote past the output")
+
+
+def _at_end(t):
+    """t's values at the end of a device allocation of its own (whole 2 MiB, so that
+    nothing is mapped by it past the tensor)."""
+    n = t.numel() * t.element_size()
+    buf = torch.empty((n // (32 << 20) + 1) * (32 << 20), dtype=torch.uint8, device="cuda")
+    v = buf[buf.numel() - n:].view(t.dtype).view(t.shape)
+    assert v.data_ptr() % 16 == 0
+    v.copy_(t)
+    return v
+
+
+@pytest.mark.parametrize("dt", [I.BF16, I.F32])
+@pytest.mark.parametrize("K", [8, 40, 72, 96, 104, 136, 192, 200, 264, 520])
+def test_reads_end_with_the_operands(K, dt):
+    """A and W at the end of their allocations, contractions shorter than a stage and
+    with a partial last one: with and without a GELU on A, many rows and few."""
+    require_gpu()
+    from paper_2604_21290_amd import api
+    for R, Co in ((1, 40), (70, 136), (20000, 20)):
+        g = np.random.default_rng(R + K)
+        x = I.store(g.standard_normal((R, K)), dt)
+        W = I.store(g.uniform(-1, 1, (Co, K)) / np.sqrt(K), dt)
+        xd, Wd = _at_end(to_dev(x)), _at_end(to_dev(W))
+        for act_in, act_out in ((0, 0), (1, 0), (0, 1)):
+            print("[gpu-test] operands' ends", R, K, Co, dt, act_in, act_out, flush=True)
+            out = api.linear(xd, Wd, None, act_in, act_out)
+            torch.cuda.synchronize()
+            ref = O.linear_ref(O.gelu_ref(x.value) if act_in else x.value, W.value)
+            check_close(from_dev(out).value, O.gelu_ref(ref) if act_out else ref, dt,
+                        f"{R} x {K} -> {Co} {act_in}{act_out}")
