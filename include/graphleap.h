@@ -91,7 +91,10 @@ typedef enum gl_schedule {
  * Position 0 is the nearest key (the node itself when keys == x and rows
  * are distinct).  Distances are ranked at fixed-point resolution
  * 2^-(30 - ceil(log2 M)) (4e-6 at M = 4096, 2.4e-7 at M = 196); keys closer
- * than that count as tied and go to the lower index.
+ * than that count as tied and go to the lower index.  Rows with a NaN or an
+ * infinity have no distance: the places that such keys take are unspecified (the
+ * same for any batch), and a list without enough other keys may hold indices up
+ * to 2^ceil(log2 M) - 1, which gl_mrconv clamps into [0, M).
  *
  *   x       [B, N, C] queries (dt).
  *   keys    [B, M, C] keys (dt), or NULL for keys = x (then M must equal N).

@@ -8,10 +8,10 @@
 //     written by ds_write.  A wave's load fills 1024 consecutive bytes of LDS, so
 //     rows cannot be padded; instead a row's 16-byte slots are permuted by its
 //     number (slot ^ (row & 7)), which spreads the 16 rows an operand read
-//     touches over all banks (0 conflicts counted).  128 bytes of K per row and
-//     stage: 64-byte rows load half cache lines and measured 25 % slower.  Two
-//     buffers, one barrier per stage: a stage's loads are issued as the one
-//     before it starts to be multiplied.
+//     touches over all banks.  128 or 256 bytes of K per row and stage: 64-byte
+//     rows load half cache lines and measured 25 % slower.  Two buffers, one
+//     barrier per stage: a stage's loads are issued as the one before it starts to
+//     be multiplied, and must arrive while it is.
 //   - MFMA operands are swapped (W rows first), so a lane ends with four
 //     consecutive output columns of one row.
 //   - Epilogue: the tile passes through LDS in fp32, wave by wave, so that
@@ -24,8 +24,8 @@
 //   - What bounds it: 128 x 128 tiles read 642 MB through L2 for the third layer
 //     below, about 21 us at the 30 TB/s that these loads reach from L2; launch,
 //     ramp and the final stores take 8-9 us of every layer.
-// Measured (us, R = 12544 = 64 images of 196 nodes; before: register-staged
-// tiles with 2-byte stores; outputs bit-identical):
+// Measured (us, cached operands, R = 12544 = 64 images of 196 nodes; before:
+// register-staged tiles with 2-byte stores; outputs bit-identical):
 //   640 -> 2560 GELU 97 -> 70, 1280 -> 640 35.6 -> 25.7,
 //   2560 -> 640 + residual 71 -> 47, 640 -> 640 + residual 29.6 -> 18.0.
 #include "gl_device.h"

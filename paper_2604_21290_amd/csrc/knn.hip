@@ -70,9 +70,8 @@ hipError_t launch_knn_tile(const KnnArgs& a, int dt_bf16, hipStream_t stream, hi
 // in-register kernel, which packs the same keys, instead of the streamed one.
 // A streamed workgroup lives for one wave's sweep of all keys, whatever the grid;
 // here four waves share the sweep of 16 rows, so time grows with the workgroups, in
-// steps of one per CU, and with the key rows that each reads from L2.  Rows of
-// whole 128-byte lines cost it most: a k-step's 64 bytes of a row are half a line,
-// and at those strides the 64 rows in flight displace the other halves in L1.
+// steps of one per CU, and with the key rows that each reads from L2 (about 6.5 TB/s
+// in all).  Rows of whole 128-byte lines are the slowest for their length.
 // us, streamed / in-register, k = 9, d = 2:
 //   bf16, M = 1024      512 tiles    768        1024      M = 4096, 1024 tiles
 //   C = 96               55 / 19    55 / 24    56 / 32    140 / 108

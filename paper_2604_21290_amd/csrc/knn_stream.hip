@@ -26,8 +26,10 @@
 //      sorted register lists (ceil(count / 16) layers of 16 per row, 16 lanes
 //      per row, the same bitonic merge as the in-register kernel), empties
 //      them and refreshes the thresholds.
-// Results are identical to the in-register kernel: the same packed keys are
-// ranked, and the threshold only skips keys that cannot enter the list.
+// Results are identical to the in-register kernel's where that builds such key
+// sets: the same packed keys are ranked, and the threshold only skips keys that
+// cannot enter the list.  A key whose distance is not a number passes no threshold
+// and is left out; places that no key takes stay all ones.
 #include "knn_tile.h"
 
 namespace gl {

@@ -30,9 +30,10 @@ hipError_t launch_ks(const MlpArgs& a, hipStream_t stream, hipEvent_t ev0, hipEv
   return launch_rt<KP, JK, NW, 2>(a, stream, ev0, ev1);
 }
 
-// Up to 192 channels the tile's rows and the ring of W fit LDS.  Past 128 that
-// leaves one workgroup per CU, and from about 25 K nodes on the separate layers,
-// whose tiles read W once per 128 nodes, are as fast (us, without and with FC1,
+// Up to 192 channels the tile's rows and the ring of W fit LDS, from 97 on with one
+// workgroup of 32 nodes per CU.  The rule is by measurement: up to 128 channels one
+// launch is faster at every size, past that the separate layers, whose tiles read W
+// once per 128 nodes, are as fast from about 25 K nodes on (us, without and with FC1,
 // layers / one launch: 6272 x 192 24.8, 29.4 / 15.3, 17.3; 12544 x 192 35.6, 42.3 /
 // 29.0, 33.0; 25088 x 160 49.1, 58.0 / 49.8, 55.3; 50176 x 192 98.5, 110 / 99.4, 108;
 // 25088 x 96 31.6, 37.6 / 21.7, 23.7; 100352 x 80 80, 92 / 63, 67;

@@ -1,8 +1,8 @@
 """Register budget of the latency-bound kernels (CPU; compiles for gfx950).
 
 The one-launch block kernel, the fused MRConv and the in-register kNN run at
-three waves per SIMD, the lean MRConv and the resident-key kNN at four or more,
-the wide kNN at two; if the register allocator has to spill to scratch memory to
+three waves per SIMD, the lean MRConv, the resident-key kNN and the direct-load
+GEMM at four or more, the wide kNN and a small grid's MRConv at two; if the register allocator has to spill to scratch memory to
 meet that, or gives a wave up, they slow down without failing any parity test.
 This test compiles their sources with the resource-usage remarks and requires no
 scratch, and the waves where they hang on registers alone, for every
@@ -18,10 +18,13 @@ import pytest
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 CSRC = os.path.join(ROOT, "paper_2604_21290_amd", "csrc")
 HIPCC = shutil.which("hipcc") or "/opt/rocm/bin/hipcc"
-KERNELS = {"block.hip": "block_kernel", "mrconv.hip": r"13mrconv_kernel|18mrconv_lean_kernel",
+KERNELS = {"block.hip": "block_kernel",
+           "mrconv.hip": r"13mrconv_kernel|mrconv_lean_kernel|mrconv_cols_kernel|mr_gather_kernel",
            "knn.hip": "knn_kernel", "knn_wide.hip": "knn_wide_kernel",
-           "knn_resident.hip": "knn_resident_kernel"}
-WAVES = {"knn.hip": 3}  # its LDS holds three workgroups' waves and more
+           "knn_resident.hip": "knn_resident_kernel", "knn_stream.hip": "knn_stream_kernel",
+           "gemm_dma.hip": "gemm_dma_kernel", "mlp.hip": "mlp_kernel"}
+# where LDS holds more workgroups than registers do
+WAVES = {"knn.hip": 3, "gemm_dma.hip": 4}
 
 
 def _usage(src: str, tmp) -> list:
